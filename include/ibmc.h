@@ -326,7 +326,9 @@ ibmc_status ibmc_check_ball_batch(ibmc_ctx *ctx, const ibmc_ball_property *props
  * cex_buf / near_tie_buf (capacities in opts), tagged with ibmc_cex.prop.
  * With stop_at_first == 0 all levels of all properties run in one
  * persistent launch per network shape, captured and replayed as one HIP
- * graph; with stop_at_first != 0 each level is launched after the previous
+ * graph (large integer workloads: one launch per shape of their reduced
+ * networks, in which the neurons that a property's domain cannot change are
+ * folded into the biases, on streams beside each other); with stop_at_first != 0 each level is launched after the previous
  * level's verdicts are known. */
 ibmc_status ibmc_check_batch(ibmc_ctx *ctx, const ibmc_property *props, int32_t n_props,
                              const ibmc_check_opts *opts, ibmc_check_summary *outs,
@@ -339,7 +341,9 @@ ibmc_status ibmc_check_batch_dev(ibmc_ctx *ctx, const ibmc_property *props, int3
 /* Stop a running check from another host thread: the kernels poll a flag in
  * host-mapped memory before taking work and drain; the check returns
  * IBMC_E_ABORTED with the counts and records of the chunks it finished (and,
- * for a resumable call, next_cursor). */
+ * for a resumable call, next_cursor; a check of reduced networks keeps whole
+ * parts of at most about 2^31 points, and one whose records were on their way
+ * to the host keeps the properties that had arrived whole). */
 ibmc_status ibmc_abort(ibmc_ctx *ctx);
 
 /* Decode (k, rank) into ascending pixels[k] and delta indices[k] (host only,
@@ -572,7 +576,8 @@ ibmc_status ibmc_tune_load(ibmc_ctx *ctx, const char *path, int32_t *n_loaded);
 /* Name of the enumeration kernel a (non-resumable) check of the network
  * launches now: a forced variant, else the tuned one for its shape, else the
  * built-in choice ("f32" for float networks); written NUL-terminated into
- * out (cap bytes). */
+ * out (cap bytes).  Unforced, large checks run most of their properties on
+ * reduced networks instead (see ibmc_check_batch). */
 ibmc_status ibmc_chosen_variant(ibmc_ctx *ctx, const ibmc_mlp *net, char *out, int64_t cap);
 /* Batches over several networks run as one HIP graph; a batch whose
  * launches match the previous one's (same plans, buffers and counter
@@ -580,7 +585,8 @@ ibmc_status ibmc_chosen_variant(ibmc_ctx *ctx, const ibmc_mlp *net, char *out, i
  * far in the context. */
 ibmc_status ibmc_graph_stats(ibmc_ctx *ctx, int64_t *launches, int64_t *reuses);
 /* Force a variant by its name (as listed by the tuner's JSON); NULL resets
- * to the built-in choice. */
+ * to the built-in choice; "fold" runs every check that allows it on reduced
+ * networks, whatever its size. */
 ibmc_status ibmc_set_variant(ibmc_ctx *ctx, const ibmc_mlp *net, const char *variant);
 /* Device time of the last enumeration kernel launches of this context, in
  * seconds, and the number of launches they span (for roofline reporting). */

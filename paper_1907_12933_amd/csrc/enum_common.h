@@ -109,17 +109,13 @@ __device__ __forceinline__ void cursor_set_q(Cursor &c) {
     c.nch = (c.seglen + CH - 1) / CH;
 }
 
-// Decode global chunk `chunk` from scratch.
+// Position of global chunk `chunk` inside its job `job`, whose fields
+// cursor_job_start has read.
 template <int CH, class PT>
-__device__ __forceinline__ void cursor_decode(Cursor &c, const PT &P, int64_t chunk) {
-    int lo = 0, hi = P.n_jobs - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if ((int64_t)wave_uniform((unsigned long long)P.jobs[mid].chunk_begin) <= chunk) lo = mid; else hi = mid - 1;
-    }
-    cursor_job_start<CH, PT>(c, P, lo);
-    const EnumJob &J = P.jobs[lo];
-    int64_t r = chunk - (int64_t)wave_uniform((unsigned long long)J.chunk_begin);
+__device__ __forceinline__ void cursor_decode_in_job(Cursor &c, const PT &P, int job, int64_t chunk) {
+    const EnumJob &J = P.jobs[job];
+    int64_t r = chunk - (int64_t)wave_uniform((unsigned long long)J.chunk_begin) +
+                (int64_t)wave_uniform((unsigned long long)J.r0);
     c.chunk = chunk;
     if (c.mode == SEG_LIST1) {
         c.q = -1; c.shell = 0;
@@ -178,6 +174,18 @@ __device__ __forceinline__ void cursor_decode(Cursor &c, const PT &P, int64_t ch
         if (j < c.k - 2) c.pre[j] = tmp[j];
         if (j == c.k - 2) c.pre[j] = c.q;
     }
+}
+
+// Decode global chunk `chunk` from scratch.
+template <int CH, class PT>
+__device__ __forceinline__ void cursor_decode(Cursor &c, const PT &P, int64_t chunk) {
+    int lo = 0, hi = P.n_jobs - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if ((int64_t)wave_uniform((unsigned long long)P.jobs[mid].chunk_begin) <= chunk) lo = mid; else hi = mid - 1;
+    }
+    cursor_job_start<CH, PT>(c, P, lo);
+    cursor_decode_in_job<CH, PT>(c, P, lo, chunk);
 }
 
 // Step a plain (k >= 2) cursor to the next segment of the same q: prefix

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cstdio>
 #include <cstdlib>
 #include <chrono>
@@ -68,7 +69,7 @@ static bool variant_matches(const EnumVariant &v, const ibmc_mlp *net) {
 const EnumVariant *pick_variant(ibmc_ctx *ctx, const ibmc_mlp *net) {
     int nv = 0;
     const EnumVariant *vs = enum_variants(&nv);
-    std::string want = net->forced_variant;
+    std::string want = net->forced_variant == kFoldVariantName ? std::string() : net->forced_variant;
     if (want.empty()) {
         auto it = ctx->tuned.find(shape_key(net));
         if (it != ctx->tuned.end()) want = it->second;
@@ -96,7 +97,7 @@ const EnumVariant *pick_variant(ibmc_ctx *ctx, const ibmc_mlp *net) {
 // only the matrix-core kernel implements (allowed false).
 bool use_lane(ibmc_ctx *ctx, const ibmc_mlp *net, bool allowed) {
     if (!allowed || !net->lane.ok) return false;
-    std::string want = net->forced_variant;
+    std::string want = net->forced_variant == kFoldVariantName ? std::string() : net->forced_variant;
     if (want.empty()) {
         auto it = ctx->tuned.find(shape_key(net));
         if (it != ctx->tuned.end()) want = it->second;
@@ -179,13 +180,17 @@ static ibmc_status validate_props(const ibmc_property *props, int32_t n_props, c
 // Sort the first n record slots on the device by (prop, k, rank) and hand
 // out the first `keep` records without the sentinels of unused slots (prop
 // -1): into `direct` when given (device memory when direct_dev, else host;
-// room for keep records), else into outv.  *nout: records handed out.
+// room for keep records), else into outv.  *nout: records handed out, of
+// *nall (fewer only where stoppable and an abort came during the transfer to
+// the host, which then stops after a piece of kAbortPiece records).
+constexpr int64_t kAbortPiece = (int64_t)1 << 20;
+
 static ibmc_status fetch_sorted(ibmc_ctx *ctx, const DevRec *drecs, int64_t n, int64_t keep, int max_prop, int max_k,
                                 int64_t max_rank, std::vector<CexRec> &outv, CexRec *direct, bool direct_dev,
-                                int64_t *nout) {
+                                bool stoppable, int64_t *nout, int64_t *nall) {
     hipStream_t s = ctx->stream;
     outv.clear();
-    *nout = 0;
+    *nout = *nall = 0;
     if (n == 0 || keep == 0) return IBMC_OK;
     IBMC_TRY(ctx->sortbuf.reserve(sort_scratch_bytes(n)));
     SortScratch S;
@@ -209,7 +214,7 @@ static ibmc_status fetch_sorted(ibmc_ctx *ctx, const DevRec *drecs, int64_t n, i
             return a.rank < b.rank;
         });
         if ((int64_t)all.size() > keep) all.resize(keep);
-        *nout = (int64_t)all.size();
+        *nout = *nall = (int64_t)all.size();
         if (direct && direct_dev) {
             HIP_OK(hipMemcpyAsync(direct, all.data(), all.size() * sizeof(CexRec), hipMemcpyHostToDevice, s));
             HIP_OK(hipStreamSynchronize(s));
@@ -231,15 +236,22 @@ static ibmc_status fetch_sorted(ibmc_ctx *ctx, const DevRec *drecs, int64_t n, i
     int64_t valid = 0;
     HIP_OK(hipMemcpyAsync(&valid, S.count, 8, hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
-    *nout = valid;
+    *nout = *nall = valid;
     if (direct_dev) return IBMC_OK;
     CexRec *hout = direct;
     if (!hout) {
         outv.resize(valid);
         hout = outv.data();
     }
-    if (valid) {
-        HIP_OK(hipMemcpyAsync(hout, dout, valid * sizeof(CexRec), hipMemcpyDeviceToHost, s));
+    // in pieces where an abort may stop the transfer
+    const int64_t piece = stoppable ? kAbortPiece : valid;
+    for (int64_t at = 0; at < valid; at += piece) {
+        if (at > 0 && ctx->flags_host[0]) {
+            *nout = at;
+            if (!direct) outv.resize(at);
+            break;
+        }
+        HIP_OK(hipMemcpyAsync(hout + at, dout + at, std::min(piece, valid - at) * sizeof(CexRec), hipMemcpyDeviceToHost, s));
         HIP_OK(hipStreamSynchronize(s));
     }
     return IBMC_OK;
@@ -261,7 +273,331 @@ struct NetPlan {
     size_t job_off = 0, n_jobs = 0;
     int grid = 0;
     int32_t packed = 0, vb_lo = 0, vb_hi = 0;
+    bool scanned = false;   // the fold scan has done these properties' clean pass
 };
+
+// Folded properties that one instance of the folded enumeration serves.
+struct FoldBucket {
+    const FoldVariant *v = nullptr;
+    std::vector<int> ids;
+    int64_t total = 0;      // chunk numbers handed out (jobs start at multiples of 4 * batch)
+    int32_t batch = 1;
+    size_t job_off = 0, n_jobs = 0;
+    int grid = 0, stage_max = 0;
+    int64_t points = 0;
+    struct Part {           // what each job covers: pixels below q_end of a (property, level)
+        int pid, li, q_end;
+        int64_t tickets;    // tickets of the launch up to the job's end
+    };
+    std::vector<Part> parts;
+};
+
+// Points of one job of a folded level at most: an aborted check keeps whole
+// jobs (tens of milliseconds each).
+constexpr int64_t kFoldJobPoints = (int64_t)1 << 31;
+
+// What folding saves is worth its extra pass (scan, one read-back, gather:
+// about 60 us) from this much estimated enumeration time on.
+constexpr double kFoldMinSeconds = 150e-6;
+constexpr size_t kFoldMaxBytes = (size_t)1 << 30;
+
+// Estimated seconds of the unfolded enumeration of one property (measured
+// rates of the matrix-core and the lane kernels on large workloads).
+static double unfolded_seconds(const ibmc_mlp *net, bool lane, int64_t points) {
+    int64_t macs = 0;
+    for (int l = 2; l <= net->L; ++l) macs += (int64_t)net->dims[l] * net->dims[l - 1];
+    return points * (lane ? 4e-12 : 12e-12 + 0.75e-15 * macs);
+}
+
+// The reduced network beats the instance the property would run on: fewer
+// matrix-core tiles per point in the hidden layers.
+static bool fold_pays(const QNetDev &q, int kw, int mt2) {
+    if (q.L == 2) return kw < q.H[1] || q.H[1] == 64;
+    return (int64_t)kw * mt2 * 16 * 4 <= (int64_t)q.H[1] * q.H[2] * 3;
+}
+
+// First-layer form of a folded property: the scale f = 2^(8 - shift -
+// halvings) that keeps every product f e w and the clamped base inside int16
+// (see enum_fold_impl.h), narrow (wide = 0) where the sum needs no saturation.
+static bool fold_scale(const ibmc_mlp *net, int maxe, int &f, int &halvings, int &wide, int &vlo, int &vhi) {
+    const int s = net->shift[0];
+    for (halvings = 0; halvings + s <= 8 && halvings <= 3; ++halvings) {
+        f = 1 << (8 - s - halvings);
+        const int64_t M = (int64_t)f * maxe * net->qd.maxw1;
+        if (halvings == 0 && M <= 8191) {
+            wide = 0;
+            vlo = (int)(-16385 - M);
+            vhi = (int)(16384 + M);
+            return true;
+        }
+        if (M <= 32767 - (1 << (14 - halvings))) {
+            wide = 1;
+            vlo = -32768;
+            vhi = 32767;
+            return true;
+        }
+    }
+    return false;
+}
+
+// Which properties of the call are folded, and by which instance.  Scans the
+// eligible networks' properties (their clean pass, their live units), reads
+// the counts back, gathers the reduced networks, and moves the folded
+// properties from the plans into buckets.  A property is folded when its
+// reduced network is clearly smaller than the kernel instance it would run
+// on; the others stay, with their clean pass done.  Nothing is folded for a
+// resumable call (its chunk numbers are part of the interface), the literal,
+// the L2 ball, a forced variant, the int32 testing aid, or when buffers come
+// from the fixed scratch array.
+static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, const ibmc_check_opts *o,
+                                   const BatchState &B, const std::vector<std::vector<int>> &level_sel, int64_t max_h1,
+                                   bool resumable, std::vector<NetPlan> &plans, std::vector<FoldBucket> &buckets) {
+    if (resumable || o->property == IBMC_PROPERTY_LITERAL || ctx->force_int32_layer1 || thread_arena()) return IBMC_OK;
+    hipStream_t s = ctx->stream;
+    struct Cand {
+        int pid, net, k, maxe;
+        int64_t points;
+    };
+    std::vector<Cand> cands;
+    std::vector<QNetDev> nets;
+    std::vector<NetPlan *> net_plan;
+    size_t ws_ints = 0, n_jobs = 0;
+    double est = 0.0;
+    for (NetPlan &pl : plans) {
+        const ibmc_mlp *net = pl.net;
+        if (net->act != IBMC_ACT_RELU_Q8 || !net->fold_ok) continue;
+        const bool forced = net->forced_variant == kFoldVariantName;
+        if (!forced && !net->forced_variant.empty()) continue;
+        const bool lane = use_lane(ctx, net, true);
+        const size_t c0 = cands.size();
+        bool any_ball = false;
+        for (int pid : pl.ids) {
+            any_ball |= B.hprops[pid].ball != 0;
+            Cand c{pid, (int)nets.size(), 0, 0, 0};
+            for (int li : level_sel[pid]) {
+                const int k = B.level_k[pid][li];
+                c.k = std::max(c.k, k);
+                ++n_jobs;
+                if (k > 0) c.points += binom_small(net->dims[0], k) * ipow64(props[pid].n_deltas, k);
+            }
+            for (int j = 0; j < props[pid].n_deltas && !B.hprops[pid].ball; ++j)
+                c.maxe = std::max(c.maxe, std::min(255, std::abs((int)props[pid].deltas[j])));
+            cands.push_back(c);
+        }
+        if (any_ball) {
+            cands.resize(c0);
+            continue;
+        }
+        for (size_t i = c0; i < cands.size(); ++i) est += forced ? kFoldMinSeconds : unfolded_seconds(net, lane, cands[i].points);
+        ws_ints += pl.ids.size() * (size_t)fold_ws(net->qd.H[1], net->L == 3 ? net->qd.H[2] : 0).total;
+        nets.push_back(net->qd);
+        net_plan.push_back(&pl);
+    }
+    // (kFoldMaxJobs: the kernel's job search)
+    if (cands.empty() || est < kFoldMinSeconds || ws_ints * 4 > kFoldMaxBytes || n_jobs > kFoldMaxJobs) return IBMC_OK;
+
+    // scan: [networks][properties][block map] in, counts and lists out
+    const size_t nc = cands.size();
+    auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    std::vector<FoldProp> fps(nc);
+    std::vector<int32_t> map;
+    IBMC_TRY(ctx->fold_ws.reserve(al(nc * 16) + ws_ints * 4));
+    int32_t *counts = ctx->fold_ws.as<int32_t>();
+    int32_t *ws = reinterpret_cast<int32_t *>(ctx->fold_ws.as<char>() + al(nc * 16));
+    for (size_t i = 0; i < nc; ++i) {
+        const Cand &c = cands[i];
+        const QNetDev &q = nets[c.net];
+        FoldProp &F = fps[i];
+        F = FoldProp{};
+        F.pid = c.pid;
+        F.net = c.net;
+        F.k = c.k;
+        for (int j = 0; j < props[c.pid].n_deltas; ++j) {
+            F.dlo = std::min<int>(F.dlo, props[c.pid].deltas[j]);
+            F.dhi = std::max<int>(F.dhi, props[c.pid].deltas[j]);
+        }
+        F.ws = ws;
+        F.counts = counts + 4 * i;
+        ws += fold_ws(q.H[1], q.L == 3 ? q.H[2] : 0).total;
+        for (int b = 0; b < q.H[1] / 64; ++b) map.push_back((int32_t)(i << 8 | b));
+    }
+    const size_t o_fp = al(nets.size() * sizeof(QNetDev)), o_map = o_fp + al(nc * sizeof(FoldProp));
+    std::vector<char> in(o_map + map.size() * 4);
+    memcpy(in.data(), nets.data(), nets.size() * sizeof(QNetDev));
+    memcpy(in.data() + o_fp, fps.data(), nc * sizeof(FoldProp));
+    memcpy(in.data() + o_map, map.data(), map.size() * 4);
+    IBMC_TRY(ctx->fold_in.upload(in.data(), in.size(), s));
+    const QNetDev *dnets = ctx->fold_in.as<QNetDev>();
+    PropDev *dprops = ctx->props.as<PropDev>();
+    HIP_OK(launch_fold_scan(dnets, reinterpret_cast<const FoldProp *>(ctx->fold_in.as<char>() + o_fp), dprops,
+                            reinterpret_cast<const int32_t *>(ctx->fold_in.as<char>() + o_map), (int)map.size(),
+                            ctx->u0.as<int32_t>(), max_h1, s));
+    std::vector<int32_t> live(4 * nc);
+    HIP_OK(hipMemcpyAsync(live.data(), counts, live.size() * 4, hipMemcpyDeviceToHost, s));
+    HIP_OK(hipStreamSynchronize(s));
+    for (NetPlan *pl : net_plan) pl->scanned = true;
+
+    int nv = 0;
+    const FoldVariant *vs = fold_variants(&nv);
+    std::vector<FoldBuild> builds;
+    std::vector<size_t> off;
+    std::vector<std::vector<int>> ids(nv);
+    std::vector<int> stage_max(nv, 0);
+    std::vector<int64_t> points(nv, 0);
+    std::vector<char> folded(B.hprops.size(), 0);
+    size_t bytes = 0;
+    for (size_t i = 0; i < nc; ++i) {
+        const Cand &c = cands[i];
+        const ibmc_mlp *net = net_plan[c.net]->net;
+        const QNetDev &q = net->qd;
+        const int live1 = live[4 * i], live2 = live[4 * i + 1], two = live[4 * i + 2], L = net->L;
+        if (c.points == 0 || live1 > kFoldMaxWidth) continue;
+        int kw = 32;
+        while (kw < live1) kw *= 2;
+        FoldBuild b{};
+        int wide = 0;
+        FoldRun &R = b.run;
+        if (!fold_scale(net, c.maxe, b.f, R.halvings, wide, R.vlo, R.vhi)) continue;
+        R.mt2 = L == 3 ? (live2 + 15) / 16 : 0;
+        R.stage_bytes = fold_stage_bytes(L, kw, R.mt2, two);
+        if (R.stage_bytes > kFoldMaxStage) continue;
+        if (net->forced_variant != kFoldVariantName && !fold_pays(q, kw, R.mt2)) continue;
+        const size_t o_v0 = bytes + al((size_t)q.dims[0] * kw * 2);
+        const size_t o_et = o_v0 + al((size_t)kw * 4);
+        const size_t o_st = o_et + al((size_t)q.dims[0] * props[c.pid].n_deltas * 2);
+        const size_t end = o_st + al(R.stage_bytes);
+        if (end > kFoldMaxBytes) continue;
+        off.insert(off.end(), {bytes, o_v0, o_et, o_st});
+        bytes = end;
+        b.pid = c.pid;
+        b.net = c.net;
+        b.kw = kw;
+        b.live1 = live1;
+        b.live2 = live2;
+        b.epi = L == 3 && net->shift[1] == 7 ? 1 : 0;
+        b.ws = fps[i].ws;
+        R.kbo = L == 3 ? (R.mt2 + 3) / 4 : 1;
+        R.two = two;
+        R.s2 = L == 3 ? net->shift[1] + 1 : 0;
+        R.label = live[4 * i + 3];
+        R.nc = q.dims[L];
+        for (int v = 0; v < nv; ++v)
+            if (vs[v].L == L && vs[v].kw == kw && vs[v].wide == wide && vs[v].epi == b.epi) {
+                ids[v].push_back(c.pid);
+                stage_max[v] = std::max(stage_max[v], R.stage_bytes);
+                points[v] += c.points;
+            }
+        folded[c.pid] = 1;
+        builds.push_back(b);
+    }
+    if (builds.empty()) return IBMC_OK;
+    IBMC_TRY(ctx->fold_data.reserve(bytes));
+    IBMC_TRY(ctx->fold_runs.reserve(al(B.hprops.size() * sizeof(FoldRun)) + builds.size() * sizeof(FoldBuild)));
+    char *base = ctx->fold_data.as<char>();
+    for (size_t i = 0; i < builds.size(); ++i) {
+        FoldRun &R = builds[i].run;
+        R.W1 = reinterpret_cast<const int16_t *>(base + off[4 * i]);
+        R.v0 = reinterpret_cast<const int32_t *>(base + off[4 * i + 1]);
+        R.etab = reinterpret_cast<const int16_t *>(base + off[4 * i + 2]);
+        R.stage = reinterpret_cast<const int8_t *>(base + off[4 * i + 3]);
+    }
+    FoldBuild *dbuilds = reinterpret_cast<FoldBuild *>(ctx->fold_runs.as<char>() + al(B.hprops.size() * sizeof(FoldRun)));
+    HIP_OK(hipMemcpyAsync(dbuilds, builds.data(), builds.size() * sizeof(FoldBuild), hipMemcpyHostToDevice, s));
+    // enough workgroups per property to fill the device with a few properties
+    const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(32, 2 * ctx->n_cu / (int64_t)builds.size()));
+    HIP_OK(launch_fold_gather(dnets, dbuilds, (int)builds.size(), parts, dprops, ctx->u0.as<int32_t>(), max_h1,
+                              ctx->fold_runs.as<FoldRun>(), s));
+    HIP_OK(hipStreamSynchronize(s));   // the staging vectors go out of scope
+    for (int v = 0; v < nv; ++v)
+        if (!ids[v].empty()) {
+            FoldBucket b;
+            b.v = &vs[v];
+            b.ids = ids[v];
+            b.stage_max = (stage_max[v] + 15) / 16 * 16;
+            b.points = points[v];
+            buckets.push_back(b);
+        }
+    std::sort(buckets.begin(), buckets.end(), [](const FoldBucket &a, const FoldBucket &b) { return a.points > b.points; });
+    // the rest stays with its network's plan; plans without properties go
+    for (NetPlan &pl : plans) {
+        std::vector<int> rest;
+        for (int pid : pl.ids)
+            if (!folded[pid]) rest.push_back(pid);
+        pl.ids.swap(rest);
+    }
+    plans.erase(std::remove_if(plans.begin(), plans.end(), [](const NetPlan &pl) { return pl.ids.empty(); }), plans.end());
+    return IBMC_OK;
+}
+
+// Chunks before level li (from its last-prefix pixel q on) of property pid in
+// the chunk order of a resumed call of these properties.
+static int64_t unfolded_chunks_before(ibmc_ctx *ctx, const ibmc_property *props, const BatchState &B,
+                                      const std::vector<std::vector<int>> &level_sel, const ibmc_mlp *net,
+                                      const std::vector<int> &ids, int pid, int li, int q) {
+    const EnumVariant *v = pick_variant(ctx, net);
+    if (!v) return 0;
+    int maxe = 0;
+    for (int i : ids)
+        for (int j = 0; j < props[i].n_deltas; ++j) maxe = std::max(maxe, std::min(255, std::abs((int)props[i].deltas[j])));
+    const int W = net->qd.f1 > 0 && (int64_t)net->qd.f1 * maxe * net->qd.maxw1 <= 8191 ? kSegGroup : 1;
+    int64_t total = 0;
+    for (int i : ids)
+        for (int l : level_sel[i]) {
+            const int k = B.level_k[i][l];
+            std::vector<int64_t> qc;
+            const bool here = i == pid && l >= li;
+            const int64_t ch = k == 0 ? 0 : plan_plain_level(net->dims[0], props[i].n_deltas, k, v->chunk, W, qc);
+            if (here && l == li && q > 0 && k >= 2) return total + (q < (int)qc.size() - 1 ? qc[q] : ch);
+            if (here) return total;
+            total += ch;
+        }
+    return total;
+}
+
+// Cuts an aborted check's results down to what lies before level li (from its
+// last-prefix pixel q on) of property pid: the counts of the levels from there
+// on (slot_cex / slot_ties hold complete parts only), the records, and the
+// chunk to resume from.
+static ibmc_status cut_results(ibmc_ctx *ctx, const ibmc_property *props, const BatchState &B,
+                               const std::vector<std::vector<int>> &level_sel, const ibmc_mlp *net,
+                               const std::vector<int> &ids, int pid, int li, int q, CexRec *direct, bool direct_dev,
+                               std::vector<CexRec> &recs, int64_t &n, std::vector<unsigned long long> &slot_cex,
+                               std::vector<unsigned long long> &slot_ties, int64_t &rec_total, int64_t *next_cursor) {
+    std::vector<CexRec> all;
+    if (direct) {
+        all.resize(n);
+        if (n) HIP_OK(hipMemcpy(all.data(), direct, n * sizeof(CexRec), direct_dev ? hipMemcpyDeviceToHost : hipMemcpyHostToHost));
+    } else {
+        all.assign(recs.begin(), recs.begin() + n);
+    }
+    const int cut_k = li < (int)B.level_k[pid].size() ? B.level_k[pid][li] : kMaxK + 1;
+    auto kept = [&](const CexRec &r) {
+        if (r.prop != pid) return r.prop < pid;
+        if (r.k != cut_k) return r.k < cut_k;
+        if (r.k < 2) return false;
+        int pix[kMaxK];
+        lex_unrank_subset(r.rank / ipow64(props[pid].n_deltas, r.k), r.k, net->dims[0], pix);
+        return pix[r.k - 2] < q;
+    };
+    all.erase(std::remove_if(all.begin(), all.end(), [&](const CexRec &r) { return !kept(r); }), all.end());
+    n = (int64_t)all.size();
+    if (direct) {
+        if (n) HIP_OK(hipMemcpy(direct, all.data(), n * sizeof(CexRec), direct_dev ? hipMemcpyHostToDevice : hipMemcpyHostToHost));
+    } else {
+        recs.swap(all);
+    }
+    for (int i : ids)
+        for (int l : level_sel[i])
+            if (i > pid || (i == pid && (l > li || (l == li && q == 0)))) {
+                slot_cex[B.slot_base[i] + l] = 0;
+                slot_ties[B.slot_base[i] + l] = 0;
+            }
+    rec_total = 0;
+    for (int i : ids)
+        for (int l : level_sel[i]) rec_total += (int64_t)slot_cex[B.slot_base[i] + l];
+    *next_cursor = unfolded_chunks_before(ctx, props, B, level_sel, net, ids, pid, li, q);
+    return IBMC_OK;
+}
 
 static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t n_props,
                               const ibmc_check_opts *o, BatchState &B,
@@ -290,7 +626,7 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
             }
         }
     }
-    const int NN = (int)plans.size();
+    int NN = (int)plans.size();
     // counters: [1] rec_count, [2] first_chunk, [3] tie_count, [4] stop flag,
     //           [8, 8+NN) per-network queues (integer matrix-core kernels),
     //           then slot_cex[n_slots], slot_ties[n_slots], slot_points[n_slots]
@@ -298,9 +634,12 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
     //           float and lane kernels: kF32Queues counters, kQueueStride apart
     const int64_t q0 = 8, sc0 = 8 + NN, st0 = sc0 + B.n_slots, sp0 = st0 + B.n_slots;
     const int64_t fq0 = (sp0 + B.n_slots + kQueueStride - 1) / kQueueStride * kQueueStride;
-    const int64_t n_ctr = fq0 + (int64_t)NN * kF32Queues * kQueueStride;
-    IBMC_TRY(ctx->counters.reserve(n_ctr * 8));
-    unsigned long long *ctr = ctx->counters.as<unsigned long long>();
+    int n_fold_inst = 0;
+    (void)fold_variants(&n_fold_inst);
+    // then one queue per instance of the folded enumeration, a line apart
+    const int64_t bq0 = fq0 + (int64_t)NN * kF32Queues * kQueueStride;
+    // and the folded jobs' counterexamples and ties
+    const int64_t fj0 = bq0 + (int64_t)n_fold_inst * kQueueStride;
     const int64_t cap = o->cex_capacity, tcap = o->near_tie_capacity;
     IBMC_TRY(ctx->ties.reserve((size_t)std::max<int64_t>(tcap, 1) * sizeof(DevRec)));
     int64_t max_h1 = 64;
@@ -310,6 +649,11 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
     std::vector<int32_t> u0_index(n_props), all_ids;
     std::iota(u0_index.begin(), u0_index.end(), 0);
     IBMC_TRY(ctx->u0_index.upload(u0_index.data(), u0_index.size() * 4, s));
+
+    std::vector<FoldBucket> buckets;
+    const std::vector<int> first_ids = plans.empty() ? std::vector<int>() : plans[0].ids;
+    const ibmc_mlp *only_net = NN == 1 ? plans[0].net : nullptr;
+    IBMC_TRY(fold_properties(ctx, props, o, B, level_sel, max_h1, resume != 0 || budget != 0, plans, buckets));
 
     // plans: variants, jobs and chunk prefix sums of every network
     std::vector<EnumJob> jobs;
@@ -385,9 +729,73 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         pl.limit = budget > 0 ? std::min(pl.total, resume + budget) : pl.total;
         all_ids.insert(all_ids.end(), pl.ids.begin(), pl.ids.end());
     }
+    int64_t n_fold_jobs = 0;
+    for (FoldBucket &b : buckets) {
+        const int CH = 16 * b.v->nt;
+        b.job_off = jobs.size();
+        int occ = 0;
+        const size_t lds = (size_t)fold_lds_bytes(*b.v, b.stage_max);
+        HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, b.v->fn, 256, lds));
+        if (occ < 1) return fail(IBMC_E_UNIMPL, "folded instance L%d width %d does not fit", b.v->L, b.v->kw);
+        for (int pass = 0; pass < 2; ++pass) {
+            // pass 0 counts the chunks, which sets the ticket size that the
+            // second pass aligns the jobs to
+            int64_t total = 0;
+            for (int pid : b.ids) {
+                const int n = props[pid].net->dims[0], m = props[pid].n_deltas;
+                for (int li : level_sel[pid]) {
+                    const int k = B.level_k[pid][li];
+                    if (k == 0) continue;
+                    // segments of one pixel in equal groups of at most kFoldGroup
+                    const int64_t per_q = k == 1 ? 1 : k == 2 ? m : (int64_t)1 << 20;
+                    const int W = (int)ceil_div(per_q, ceil_div(per_q, kFoldGroup));
+                    std::vector<int64_t> qc;
+                    const int64_t ch = plan_plain_level(n, m, k, CH, W, qc);
+                    if (pass == 0) {
+                        total += ch;
+                        continue;
+                    }
+                    const int64_t T = 4 * (int64_t)b.batch;
+                    const int64_t cut = std::max(kFoldJobPoints / ((int64_t)CH * W), ch / 256);
+                    const size_t qo = k >= 2 ? qcum_all.size() : (size_t)-1;
+                    if (k >= 2) qcum_all.insert(qcum_all.end(), qc.begin(), qc.end());
+                    int64_t from = 0;
+                    for (int q = k >= 2 ? k - 2 : n - 2; q <= n - 2; ++q) {
+                        const int64_t to = q + 1 <= n - 2 ? qc[q + 1] : ch;
+                        if (to - from < cut && q < n - 2) continue;
+                        total = ceil_div(total, T) * T;
+                        EnumJob J{};
+                        J.prop = pid;
+                        J.k = k;
+                        J.slot = (int)(n_fold_jobs++);
+                        J.mode = SEG_PLAIN;
+                        J.wseg = W;
+                        J.r0 = from;
+                        J.chunk_begin = total;
+                        J.chunk_end = total + (to - from);
+                        total = J.chunk_end;
+                        from = to;
+                        qcum_off.push_back(qo);
+                        jobs.push_back(J);
+                        b.parts.push_back({pid, li, q + 1, ceil_div(total, T)});
+                    }
+                }
+            }
+            b.total = total;
+            // about eight tickets per workgroup, at most 16 chunks per wave and ticket
+            const int64_t wgs = (int64_t)ctx->n_cu * occ;
+            if (pass == 0) b.batch = (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, total / (wgs * 4 * 8)));
+            else b.grid = (int)std::min<int64_t>(wgs, std::max<int64_t>(1, ceil_div(total, 4 * (int64_t)b.batch)));
+        }
+        b.n_jobs = jobs.size() - b.job_off;
+    }
+    const int64_t n_ctr = fj0 + 2 * n_fold_jobs;
+    IBMC_TRY(ctx->counters.reserve(n_ctr * 8));
+    unsigned long long *ctr = ctx->counters.as<unsigned long long>();
     // record slots: the capacity plus one partly used block per wave of the
     // integer kernels (whose unused slots hold sentinels)
     int64_t rec_slots = cap;
+    for (const FoldBucket &b : buckets) rec_slots += (int64_t)b.grid * 4 * kRecBlock;
     for (auto &pl : plans)
         if (pl.net->act == IBMC_ACT_RELU_Q8 && !pl.lane) rec_slots += (int64_t)pl.grid * 4 * kRecBlock;
     IBMC_TRY(ctx->recs.reserve((size_t)std::max<int64_t>(rec_slots, 1) * sizeof(DevRec)));
@@ -399,7 +807,8 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
     // (no jobs at all: every selected level is k = 0 or empty)
     if (jobs.empty()) IBMC_TRY(ctx->jobs.reserve(sizeof(EnumJob)));
     else IBMC_TRY(ctx->jobs.upload(jobs.data(), jobs.size() * sizeof(EnumJob), s));
-    IBMC_TRY(ctx->prop_ids.upload(all_ids.data(), std::max<size_t>(all_ids.size(), 1) * 4, s));
+    if (all_ids.empty()) IBMC_TRY(ctx->prop_ids.reserve(4));
+    else IBMC_TRY(ctx->prop_ids.upload(all_ids.data(), all_ids.size() * 4, s));
     HIP_OK(hipStreamSynchronize(s));  // host staging vectors may go now
 
     PropDev *dprops = ctx->props.as<PropDev>();
@@ -417,11 +826,13 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
     const bool literal = o->property == IBMC_PROPERTY_LITERAL;
     // One network: the enumeration launch alone is bracketed by ek0 / ek1
     // (the kernel time reported for rooflines); several: the whole graph.
-    const bool time_enum = NN <= 1;
+    NN = (int)plans.size();
+    const bool time_enum = NN + (int)buckets.size() <= 1;
     // the clean pass of a network's properties, and its enumeration launch
     auto launch_clean = [&](const NetPlan &pl, size_t id_off, hipStream_t st) -> ibmc_status {
         const ibmc_mlp *net = pl.net;
         const int32_t *ids = ctx->prop_ids.as<int32_t>() + id_off;
+        if (pl.scanned) return IBMC_OK;
         if (net->act == IBMC_ACT_RELU_Q8)
             HIP_OK(launch_clean_q8(net->qd, dprops, ids, (int32_t)pl.ids.size(), ctx->u0.as<int32_t>(), max_h1, st));
         else
@@ -522,11 +933,74 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         return IBMC_OK;
     };
 
+    auto launch_bucket = [&](const FoldBucket &b, hipStream_t st) -> ibmc_status {
+        const int bi = (int)(&b - buckets.data());
+        FoldParams P{};
+        P.jobs = ctx->jobs.as<EnumJob>() + b.job_off;
+        P.n_jobs = (int32_t)b.n_jobs;
+        P.batch = b.batch;
+        P.total_chunks = b.total;
+        P.props = dprops;
+        P.runs = ctx->fold_runs.as<FoldRun>();
+        P.stage_max = b.stage_max;
+        P.queue = ctr + bq0 + (int64_t)bi * kQueueStride;
+        P.rec_count = ctr + 1;
+        P.rec_cap = rec_slots;
+        P.recs = ctx->recs.as<DevRec>();
+        P.slot_cex = ctr + fj0;
+        P.slot_ties = ctr + fj0 + n_fold_jobs;
+        P.abort_host = ctx->flags_dev;
+        if (time_enum) HIP_OK(hipEventRecord(ctx->ek0, st));
+        HIP_OK(launch_enum_fold(*b.v, b.grid, P, st));
+        if (time_enum) HIP_OK(hipEventRecord(ctx->ek1, st));
+        return IBMC_OK;
+    };
+    // one more private stream (and its event) per concurrent branch
+    auto need_streams = [&](int n) -> ibmc_status {
+        while ((int)ctx->side.size() < n) {
+            hipStream_t ns;
+            HIP_OK(hipStreamCreateWithFlags(&ns, hipStreamNonBlocking));
+            ctx->side.push_back(ns);
+            hipEvent_t ev;
+            HIP_OK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+            ctx->side_ev.push_back(ev);
+        }
+        if (!ctx->fork_ev) HIP_OK(hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming));
+        return IBMC_OK;
+    };
+
     kernel_seconds = 0.0;
     launches = 0;
     bool timed = false;
     if (!time_enum) HIP_OK(hipEventRecord(ctx->ek0, s));
-    if (NN <= 1) {
+    if (!buckets.empty()) {
+        // Folded properties: which instances run depends on the images, so the
+        // launches are not captured; the largest bucket runs on the
+        // context's stream, the others beside it.
+        HIP_OK(launch_fill_u64(ctr, n_ctr, 0ull, s));
+        HIP_OK(launch_fill_u64(ctr + 2, 1, ~0ull, s));
+        size_t id_off = 0;
+        for (auto &pl : plans) {
+            IBMC_TRY(launch_clean(pl, id_off, s));
+            id_off += pl.ids.size();
+        }
+        const int branches = (int)buckets.size() + NN;
+        if (branches > 1) {
+            IBMC_TRY(need_streams(branches));
+            HIP_OK(hipEventRecord(ctx->fork_ev, s));
+        }
+        ibmc_status bst = IBMC_OK;
+        for (int i = 0; i < branches; ++i) {
+            hipStream_t st = i == 0 ? s : ctx->side[i];
+            if (i > 0) HIP_OK(hipStreamWaitEvent(st, ctx->fork_ev, 0));
+            if (bst == IBMC_OK)
+                bst = i < (int)buckets.size() ? launch_bucket(buckets[i], st) : launch_net(plans[i - buckets.size()], st);
+            if (i > 0) HIP_OK(hipEventRecord(ctx->side_ev[i], st));
+        }
+        for (int i = 1; i < branches; ++i) HIP_OK(hipStreamWaitEvent(s, ctx->side_ev[i], 0));
+        IBMC_TRY(bst);
+        timed = true;
+    } else if (NN <= 1) {
         HIP_OK(launch_fill_u64(ctr, n_ctr, 0ull, s));
         HIP_OK(launch_fill_u64(ctr + 2, 1, ~0ull, s));
         size_t id_off = 0;
@@ -539,15 +1013,7 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
     } else {
         // one graph: counters cleared by a kernel (no memset node), then a
         // branch per network on its own stream, joined back into s
-        while ((int)ctx->side.size() < NN) {
-            hipStream_t ns;
-            HIP_OK(hipStreamCreateWithFlags(&ns, hipStreamNonBlocking));
-            ctx->side.push_back(ns);
-            hipEvent_t ev;
-            HIP_OK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-            ctx->side_ev.push_back(ev);
-        }
-        if (!ctx->fork_ev) HIP_OK(hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming));
+        IBMC_TRY(need_streams(NN));
         hipStream_t cs = ctx->side[0];  // capture origin: a private stream, never the caller's
         HIP_OK(hipStreamWaitEvent(cs, ctx->ek0, 0));
         // Every value the captured launches read: the plans, the buffers
@@ -653,7 +1119,7 @@ graph_done:
         HIP_OK(hipEventElapsedTime(&ms, ctx->ek0, ctx->ek1));
     }
     kernel_seconds = ms * 1e-3;
-    launches = timed ? NN : 0;
+    launches = timed ? NN + (int)buckets.size() : 0;
     // gather
     std::vector<unsigned long long> h(n_ctr);
     HIP_OK(hipMemcpyAsync(h.data(), ctr, n_ctr * 8, hipMemcpyDeviceToHost, s));
@@ -663,7 +1129,7 @@ graph_done:
         // every queue ticket handed out was worked through: chunks below
         // resume + tickets * batch are done
         *next_cursor = -1;
-        if (NN == 1 && plans[0].net->act == IBMC_ACT_RELU_Q8 && !plans[0].lane) {
+        if (NN == 1 && buckets.empty() && plans[0].net->act == IBMC_ACT_RELU_Q8 && !plans[0].lane) {
             const NetPlan &pl = plans[0];
             const int64_t done = std::min<int64_t>(pl.limit, resume + (int64_t)h[q0] * pl.batch);
             if (done < pl.total) *next_cursor = done;
@@ -672,6 +1138,40 @@ graph_done:
     slot_cex.assign(h.begin() + sc0, h.begin() + st0);
     slot_ties.assign(h.begin() + st0, h.begin() + sp0);
     slot_points.assign(h.begin() + sp0, h.begin() + sp0 + B.n_slots);
+    // An aborted check of one integer network returns a prefix of its
+    // properties and levels, from whose end a resumed call continues: `cut`
+    // is the first part that is not in it (by property, level, pixel).
+    struct Cut {
+        int pid = -1, li = 0, q = 0;
+    } cut;
+    const bool may_cut = next_cursor && only_net && !buckets.empty();
+    {
+        std::vector<std::array<int, 4>> parts;   // property, level, end pixel, complete
+        for (const FoldBucket &b : buckets)
+            for (size_t j = 0; j < b.parts.size(); ++j) {
+                const FoldBucket::Part &pt = b.parts[j];
+                const int slot = B.slot_base[pt.pid] + pt.li;
+                const bool done = pt.tickets <= (int64_t)h[bq0 + (&b - buckets.data()) * kQueueStride];
+                const int64_t fj = jobs[b.job_off + j].slot;
+                if (may_cut) parts.push_back({pt.pid, pt.li, pt.q_end, done ? 1 : 0});
+                if (!may_cut || done) {
+                    slot_cex[slot] += h[fj0 + fj];
+                    slot_ties[slot] += h[fj0 + n_fold_jobs + fj];
+                }
+            }
+        if (may_cut && ctx->flags_host[0]) {
+            for (const NetPlan &pl : plans)   // properties that were not folded: all of them or none
+                for (int pid : pl.ids)
+                    parts.push_back({pid, 0, 0, (int64_t)h[q0] * pl.batch >= pl.total && !pl.lane ? 1 : 0});
+            std::sort(parts.begin(), parts.end());
+            int from = 0;   // where the last incomplete part starts
+            for (size_t j = 0; j < parts.size() && cut.pid < 0; ++j) {
+                if (!parts[j][3]) cut = {parts[j][0], parts[j][1], from};
+                const bool more = j + 1 < parts.size() && parts[j + 1][0] == parts[j][0] && parts[j + 1][1] == parts[j][1];
+                from = more ? parts[j][2] : 0;
+            }
+        }
+    }
     // exact total from the level counters; record slots handed out (with the
     // sentinels of partly used blocks) from the record counter
     rec_total = 0;
@@ -685,11 +1185,19 @@ graph_done:
         const int pid = J.prop;
         max_rank = std::max(max_rank, binom_small(props[pid].net->dims[0], J.k) * ipow64(props[pid].n_deltas, J.k));
     }
-    int64_t nout = 0;
+    int64_t nout = 0, nall = 0;
     IBMC_TRY(fetch_sorted(ctx, ctx->recs.as<DevRec>(), nr, cap, n_props - 1, max_k, max_rank, recs, direct_recs,
-                          direct_dev, &nout));
+                          direct_dev, may_cut && cut.pid < 0 && rec_total <= cap, &nout, &nall));
+    if (nout < nall && cut.pid < 0) {
+        // aborted while the records came back: the last record's property is not whole
+        const CexRec *r = direct_recs ? direct_recs : recs.data();
+        cut = {nout ? r[nout - 1].prop : 0, 0, 0};
+    }
+    if (cut.pid >= 0)
+        IBMC_TRY(cut_results(ctx, props, B, level_sel, only_net, first_ids, cut.pid, cut.li, cut.q, direct_recs,
+                             direct_dev, recs, nout, slot_cex, slot_ties, rec_total, next_cursor));
     IBMC_TRY(fetch_sorted(ctx, ctx->ties.as<DevRec>(), nt, tcap, n_props - 1, max_k, max_rank, ties, direct_ties,
-                          direct_dev, &nout));
+                          direct_dev, false, &nout, &nall));
     HIP_OK(hipMemcpyAsync(B.hprops.data(), ctx->props.p, n_props * sizeof(PropDev), hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
     if (ctx->flags_host[0]) return fail(IBMC_E_ABORTED, "check aborted");
@@ -1069,6 +1577,12 @@ extern "C" ibmc_status ibmc_set_variant(ibmc_ctx *ctx, const ibmc_mlp *net, cons
     if (!ctx || !net) return fail(IBMC_E_INVALID, "null argument");
     ibmc_mlp *m = const_cast<ibmc_mlp *>(net);
     if (!variant) { m->forced_variant.clear(); return IBMC_OK; }
+    if (std::string(variant) == kFoldVariantName) {
+        if (net->act != IBMC_ACT_RELU_Q8 || !net->fold_ok)
+            return fail(IBMC_E_INVALID, "variant %s does not match the network", variant);
+        m->forced_variant = variant;
+        return IBMC_OK;
+    }
     if (std::string(variant) == kLaneVariantName) {
         if (!net->lane.ok) return fail(IBMC_E_INVALID, "variant %s does not match the network", variant);
         m->forced_variant = variant;
@@ -1092,6 +1606,8 @@ extern "C" ibmc_status ibmc_chosen_variant(ibmc_ctx *ctx, const ibmc_mlp *net, c
     std::string name;
     if (net->act != IBMC_ACT_RELU_Q8) {
         name = "f32";
+    } else if (net->forced_variant == kFoldVariantName) {
+        name = kFoldVariantName;
     } else if (use_lane(ctx, net, true)) {
         name = kLaneVariantName;
     } else {
@@ -1367,9 +1883,9 @@ ibmc_status ordered_search(ibmc_ctx *ctx, const ibmc_mlp *net, const ibmc_propos
     for (int li = 0; li < n_slots; ++li) rec_total += (int64_t)h[8 + li];
     const int64_t nr = std::min((int64_t)h[1], rec_slots);
     std::vector<CexRec> recs;
-    int64_t nkept = 0;
+    int64_t nkept = 0, nall = 0;
     IBMC_TRY(fetch_sorted(ctx, ctx->recs.as<DevRec>(), nr, cap, 0, o->k_max, binom_small(n, 2) * m * m, recs, nullptr,
-                          false, &nkept));
+                          false, false, &nkept, &nall));
     if (p) {
         order.resize(N1);
         HIP_OK(hipMemcpy(order.data(), ctx->order.p, N1 * 4, hipMemcpyDeviceToHost));

@@ -16,6 +16,7 @@
 #include "kernels_prop.h"
 #include "kernels_sort.h"
 #include "kernels_lane.h"
+#include "kernels_fold.h"
 
 namespace ibmc {
 
@@ -88,6 +89,7 @@ struct ibmc_ctx {
     ibmc::DevBuf images, props, jobs, qcum, u0, u0_index, prop_ids, counters, recs, ties, order;
     ibmc::DevBuf u0f, sortbuf;
     ibmc::DevBuf lut;                  // the table sigmoid's knots (built on first use)
+    ibmc::DevBuf fold_in, fold_ws, fold_runs, fold_data;   // folded properties: see run_levels
     ibmc::DevBuf recout;  // sorted records in the public layout, on their way to a host buffer
     ibmc::DevBuf prop_scratch, prop_feat, prop_scores, shell_cum;  // ranked search
     int64_t shell_cum_n = -1, shell_cum_ch = -1;                   // shell_cum holds this plan
@@ -132,6 +134,7 @@ struct ibmc_mlp {
     ibmc::FwdExtra fx;
     ibmc::FNetDev fd;
     ibmc::LaneNetDev lane{};           // integer nets the lane kernels serve (lane.ok)
+    bool fold_ok = false;              // integer nets whose properties may be folded
     std::string forced_variant;
     ~ibmc_mlp();
 };

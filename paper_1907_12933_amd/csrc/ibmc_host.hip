@@ -358,6 +358,18 @@ static ibmc_status build_q8(ibmc_ctx *ctx, ibmc_mlp *m) {
         IBMC_TRY(m->buf.emplace_back().upload(t.data(), t.size(), s));
         q.W1tile = (const int8_t *)m->buf.back().p;
     }
+    // properties may be folded: the enumeration's shapes, a first layer whose
+    // requantiser window fits 16 bits, and room in int32 for the later
+    // layers' doubled inputs, folded biases and logit differences (each at
+    // most 8 times |b| + 256 sum |w|)
+    m->fold_ok = (L == 2 || L == 3) && m->dims[L] <= 16 && m->shift[0] <= 8;
+    for (int l = 2; l <= L && m->fold_ok; ++l)
+        for (int j = 0; j < m->dims[l] && m->fold_ok; ++j) {
+            int64_t sa = 0;
+            for (int i = 0; i < m->dims[l - 1]; ++i) sa += std::abs((int)m->Wq[l - 1][(size_t)j * m->dims[l - 1] + i]);
+            const int64_t bound = std::llabs((long long)m->bq[l - 1][j]) + 256 * sa + (l < L ? (int64_t)64 << m->shift[l - 1] : 0);
+            if (bound >= (1LL << 27)) m->fold_ok = false;
+        }
     // fast hidden epilogue of 3-layer nets (shift[1] in {7, 8}), where every
     // partial sum of its offset accumulators stays inside int32
     bool fast_ok = L == 3 && (m->shift[1] == 7 || m->shift[1] == 8);

@@ -165,6 +165,7 @@ struct EnumJob {
     const int64_t *qcum;   // plain k >= 2: chunks before last-prefix pixel q, [n]
     const int32_t *order;  // shell / list modes: candidate ids (p * m + i) by decreasing score
     const int64_t *shell_cum; // shell mode: chunks before shell t, [n*m + 1]
+    int64_t r0;            // chunks of the level before this job's first (a level cut into several jobs)
     int32_t wseg;          // plain k >= 2: segments per group (one chunk covers the same
                            // last-element positions of wseg consecutive segments); else 1
     int32_t pad_;

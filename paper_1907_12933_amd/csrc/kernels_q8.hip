@@ -4,6 +4,7 @@
 #include <vector>
 
 #include "kernels_q8.h"
+#include "kernels_fold.h"
 #include "enum_common.h"
 
 namespace ibmc {
@@ -251,6 +252,190 @@ __global__ void __launch_bounds__(kCleanThreads) clean_q8_kernel(QNetDev net, Pr
     }
 }
 
+// Scan of the folded properties: the clean pass of clean_q8_kernel with, per
+// first-layer unit, the largest and smallest change that one perturbed pixel
+// can make (every delta between the smallest and the largest, clamped to
+// [0, 255] with the pixel).  k of them bound the potential over the whole
+// domain; the block that completes a property's slices turns the bounds into
+// activation intervals, carries them through the second hidden layer, and
+// writes the live units (interval of more than one value), the biases with
+// the constant units folded in, and the counts.  Latency-bound: one weight
+// pass over the first layer (as the clean pass) and one over the later ones.
+constexpr int kScanSlice = 64;
+
+__global__ void __launch_bounds__(kCleanThreads) fold_scan_kernel(const QNetDev *nets, const FoldProp *fps,
+                                                                  PropDev *props, const int32_t *block_map,
+                                                                  int32_t *u0_store, int64_t u0_stride) {
+    __shared__ int a0[kMaxWidth], a1[kMaxWidth];
+    __shared__ int part[3 * 64][kScanSlice];
+    static_assert(sizeof(part) >= sizeof(int) * kFwdSplit * kMaxWidth, "dense tail scratch");
+    __shared__ int lab, tie, last, cnt[16], two;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const FoldProp F = fps[block_map[blockIdx.x] >> 8];
+    const int w = block_map[blockIdx.x] & 0xff;
+    const QNetDev &net = nets[F.net];
+    const int n = net.dims[0], H1 = net.H[1], L = net.L, h1 = net.dims[1];
+    const int S = H1 / kScanSlice, G1 = H1 / 4;
+    const FoldWs ws = fold_ws(H1, L == 3 ? net.H[2] : 0);
+    const uint8_t *x = props[F.pid].image;
+    int32_t *u0s = u0_store + (int64_t)F.pid * u0_stride;
+    {
+        // 16 groups of four units, 64 pixel segments
+        const int grp = tid & 15, sg = tid >> 4;
+        const int seg = (n + 63) / 64;
+        const int i0 = sg * seg, i1 = min(n, i0 + seg);
+        const int *w4 = reinterpret_cast<const int *>(net.W1T) + w * 16 + grp;
+        int u[4] = {0, 0, 0, 0}, up[4] = {0, 0, 0, 0}, dn[4] = {0, 0, 0, 0};
+#pragma unroll 8
+        for (int i = i0; i < i1; ++i) {
+            const int wd = w4[(int64_t)i * G1];
+            const int xv = x[i];
+            const int eh = min(xv + F.dhi, 255) - xv, el = max(xv + F.dlo, 0) - xv;   // eh >= 0 >= el
+#pragma unroll
+            for (int z = 0; z < 4; ++z) {
+                const int c = (int)(int8_t)(wd >> (8 * z));
+                u[z] += c * xv;
+                const int p = c * eh, q = c * el;
+                up[z] = max(up[z], max(p, q));
+                dn[z] = min(dn[z], min(p, q));
+            }
+        }
+#pragma unroll
+        for (int z = 0; z < 4; ++z) {
+            part[sg][4 * grp + z] = u[z];
+            part[64 + sg][4 * grp + z] = up[z];
+            part[128 + sg][4 * grp + z] = dn[z];
+        }
+        __syncthreads();
+        if (tid < 3 * kScanSlice) {
+            const int what = tid >> 6, q = w * kScanSlice + lane;
+            int v = what == 0 ? net.b1s[q] : 0;
+            for (int t = 0; t < 64; ++t) {
+                const int pv = part[64 * what + t][lane];
+                v = what == 0 ? v + pv : what == 1 ? max(v, pv) : min(v, pv);
+            }
+            if (what == 0) u0s[q] = v;
+            else F.ws[(what == 1 ? ws.ub : ws.lb) + q] = v;
+        }
+    }
+    // publish the slice, then count it (release); the block that completes
+    // the count sees every slice (acquire)
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) last = (atomicAdd(&props[F.pid].clean_done, 1) + 1) % S == 0;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    for (int q = tid; q < H1; q += blockDim.x) {
+        const int neuron = sigma64(q);
+        if (neuron < h1) a0[neuron] = requant_relu(u0s[q], net.shift[0]);
+    }
+    __syncthreads();
+    dense_tail_block(net, a0, a1, reinterpret_cast<int (*)[kMaxWidth]>(&part[0][0]), nullptr, &lab, &tie);
+    __syncthreads();
+    if (tid == 0) {
+        props[F.pid].label0 = lab;
+        props[F.pid].tie0 = tie;
+        two = 0;
+    }
+    int *const alo = a0, *const ahi = a1;            // activation intervals, natural order
+    int *const blo = &part[0][0], *const bhi = blo + kMaxWidth;   // of the second hidden layer
+
+    // appends the indices whose flag is set to list, in index order; returns
+    // their number
+    auto compact = [&](bool flag, int value, int32_t *list) -> int {
+        const unsigned long long m = __ballot(flag);
+        if (lane == 0) cnt[wv] = __popcll(m);
+        __syncthreads();
+        int before = 0, all = 0;
+        for (int t = 0; t < 16; ++t) {
+            before += t < wv ? cnt[t] : 0;
+            all += cnt[t];
+        }
+        if (flag) list[before + __popcll(m & ((1ull << lane) - 1ull))] = value;
+        __syncthreads();
+        return all;
+    };
+    // layer 1 (H1 <= 1024 threads): 64-bit bounds, they may leave int32
+    bool live = false;
+    if (tid < H1) {
+        const int neuron = sigma64(tid);
+        if (neuron < h1) {
+            const int64_t u = u0s[tid];
+            const int64_t hi = (u + (int64_t)F.k * F.ws[ws.ub + tid]) >> net.shift[0];
+            const int64_t lo = (u + (int64_t)F.k * F.ws[ws.lb + tid]) >> net.shift[0];
+            const int ih = (int)min((int64_t)127, max((int64_t)0, hi)), il = (int)min((int64_t)127, max((int64_t)0, lo));
+            ahi[neuron] = ih;
+            alo[neuron] = il;
+            live = ih != il;
+        }
+    }
+    const int live1 = compact(live, tid, F.ws + ws.list1);
+    // one later layer's rows: bias with the constant inputs, sum of the live
+    // inputs' weights, and (hidden) the potential's interval; a wave per row
+    auto rows = [&](int l, int nin, int nout, const int *il, const int *ih, int32_t *bf, int32_t *rs, int *ol,
+                    int *oh) {
+        for (int r = wv; r < nout; r += 16) {
+            const int8_t *row = net.Wd[l] + (int64_t)r * nin;
+            int cs = 0, sum = 0, lo = 0, hi = 0;
+            for (int i = lane; i < nin; i += 64) {
+                const int c = row[i], a = il[i], b = ih[i];
+                if (a == b) {
+                    cs += c * a;
+                } else {
+                    sum += c;
+                    lo += min(c * a, c * b);
+                    hi += max(c * a, c * b);
+                }
+            }
+            for (int d = 32; d > 0; d >>= 1) {
+                cs += __shfl_xor(cs, d);
+                sum += __shfl_xor(sum, d);
+                lo += __shfl_xor(lo, d);
+                hi += __shfl_xor(hi, d);
+            }
+            if (lane == 0) {
+                const int b = net.bd[l][r] + cs;
+                bf[r] = b;
+                rs[r] = sum;
+                if (ol) {
+                    ol[r] = requant_relu(b + lo, net.shift[l - 1]);
+                    oh[r] = requant_relu(b + hi, net.shift[l - 1]);
+                }
+            }
+        }
+        __syncthreads();
+    };
+    int live2 = 0;
+    if (L == 3) {
+        const int h2 = net.dims[2];
+        rows(2, h1, h2, alo, ahi, F.ws + ws.b2, F.ws + ws.rs2, blo, bhi);
+        live2 = compact(tid < h2 && blo[tid < h2 ? tid : 0] != bhi[tid < h2 ? tid : 0], tid, F.ws + ws.list2);
+        rows(3, h2, net.dims[3], blo, bhi, F.ws + ws.bo, F.ws + ws.rso, nullptr, nullptr);
+    } else {
+        rows(2, h1, net.dims[2], alo, ahi, F.ws + ws.bo, F.ws + ws.rso, nullptr, nullptr);
+    }
+    // does a weight difference to the label's row leave int8 on a live input?
+    const int hl = net.dims[L - 1], nc = net.dims[L];
+    const int *il = L == 3 ? blo : alo, *ih = L == 3 ? bhi : ahi;
+    bool wide = false;
+    for (int t = tid; t < nc * hl; t += blockDim.x) {
+        const int i = t % hl;
+        if (il[i] != ih[i]) {
+            const int d = (int)net.Wd[L][t] - (int)net.Wd[L][(int64_t)lab * hl + i];
+            wide |= d < -128 || d > 127;
+        }
+    }
+    if (wide) two = 1;
+    __syncthreads();
+    if (tid == 0) {
+        F.counts[0] = live1;
+        F.counts[1] = live2;
+        F.counts[2] = two;
+        F.counts[3] = lab;
+    }
+}
+
 // Replay: rebuild each perturbed image from its record and run the plain
 // forward pass.
 __global__ void __launch_bounds__(kFwdThreads) replay_q8_kernel(QNetDev net, const uint8_t *clean,
@@ -340,6 +525,14 @@ hipError_t launch_clean_q8(const QNetDev &net, PropDev *props, const int32_t *pr
     if (net.H[1] % 16) return hipErrorInvalidValue;
     const int grid = (int)std::min<int64_t>((int64_t)n_ids * (net.H[1] / clean_slice(net.H[1])), 8192);
     hipLaunchKernelGGL(clean_q8_kernel, dim3(grid), dim3(kCleanThreads), 0, s, net, props, prop_ids, n_ids,
+                       u0_store, u0_stride);
+    return hipGetLastError();
+}
+
+hipError_t launch_fold_scan(const QNetDev *nets, const FoldProp *fps, PropDev *props, const int32_t *block_map,
+                            int n_blocks, int32_t *u0_store, int64_t u0_stride, hipStream_t s) {
+    if (n_blocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(fold_scan_kernel, dim3(n_blocks), dim3(kCleanThreads), 0, s, nets, fps, props, block_map,
                        u0_store, u0_stride);
     return hipGetLastError();
 }
