@@ -311,9 +311,9 @@ static double unfolded_seconds(const ibmc_mlp *net, bool lane, int64_t points) {
 
 // The reduced network beats the instance the property would run on: fewer
 // matrix-core tiles per point in the hidden layers.
-static bool fold_pays(const QNetDev &q, int kw, int mt2) {
+static bool fold_pays(const QNetDev &q, int kw, int npair) {
     if (q.L == 2) return kw < q.H[1] || q.H[1] == 64;
-    return (int64_t)kw * mt2 * 16 * 4 <= (int64_t)q.H[1] * q.H[2] * 3;
+    return (int64_t)kw * npair * 32 * 4 <= (int64_t)q.H[1] * q.H[2] * 3;
 }
 
 // First-layer form of a folded property: the scale f = 2^(8 - shift -
@@ -400,7 +400,7 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
     const size_t nc = cands.size();
     auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
     std::vector<FoldProp> fps(nc);
-    std::vector<int32_t> map;
+    std::vector<int32_t> map, rmap;
     IBMC_TRY(ctx->fold_ws.reserve(al(nc * 16) + ws_ints * 4));
     int32_t *counts = ctx->fold_ws.as<int32_t>();
     int32_t *ws = reinterpret_cast<int32_t *>(ctx->fold_ws.as<char>() + al(nc * 16));
@@ -416,12 +416,16 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
             F.dlo = std::min<int>(F.dlo, props[c.pid].deltas[j]);
             F.dhi = std::max<int>(F.dhi, props[c.pid].deltas[j]);
         }
+        F.joint = net_plan[c.net]->net->fold_joint ? 1 : 0;
         F.ws = ws;
         F.counts = counts + 4 * i;
         ws += fold_ws(q.H[1], q.L == 3 ? q.H[2] : 0).total;
         for (int b = 0; b < q.H[1] / 64; ++b) map.push_back((int32_t)(i << 8 | b));
+        for (int b = 0; q.L == 3 && b < (q.dims[2] + 63) / 64; ++b) rmap.push_back((int32_t)(i << 8 | b));
     }
     const size_t o_fp = al(nets.size() * sizeof(QNetDev)), o_map = o_fp + al(nc * sizeof(FoldProp));
+    const size_t n_scan = map.size();
+    map.insert(map.end(), rmap.begin(), rmap.end());
     std::vector<char> in(o_map + map.size() * 4);
     memcpy(in.data(), nets.data(), nets.size() * sizeof(QNetDev));
     memcpy(in.data() + o_fp, fps.data(), nc * sizeof(FoldProp));
@@ -429,9 +433,10 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
     IBMC_TRY(ctx->fold_in.upload(in.data(), in.size(), s));
     const QNetDev *dnets = ctx->fold_in.as<QNetDev>();
     PropDev *dprops = ctx->props.as<PropDev>();
-    HIP_OK(launch_fold_scan(dnets, reinterpret_cast<const FoldProp *>(ctx->fold_in.as<char>() + o_fp), dprops,
-                            reinterpret_cast<const int32_t *>(ctx->fold_in.as<char>() + o_map), (int)map.size(),
-                            ctx->u0.as<int32_t>(), max_h1, s));
+    const FoldProp *dfps = reinterpret_cast<const FoldProp *>(ctx->fold_in.as<char>() + o_fp);
+    const int32_t *dmap = reinterpret_cast<const int32_t *>(ctx->fold_in.as<char>() + o_map);
+    HIP_OK(launch_fold_scan(dnets, dfps, dprops, dmap, (int)n_scan, ctx->u0.as<int32_t>(), max_h1, s));
+    HIP_OK(launch_fold_bound(dnets, dfps, dprops, dmap + n_scan, (int)rmap.size(), s));
     std::vector<int32_t> live(4 * nc);
     HIP_OK(hipMemcpyAsync(live.data(), counts, live.size() * 4, hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
@@ -450,18 +455,19 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
         const Cand &c = cands[i];
         const ibmc_mlp *net = net_plan[c.net]->net;
         const QNetDev &q = net->qd;
-        const int live1 = live[4 * i], live2 = live[4 * i + 1], two = live[4 * i + 2], L = net->L;
+        const int live1 = live[4 * i], live2 = live[4 * i + 1] & 0xffff, two = live[4 * i + 2], L = net->L;
         if (c.points == 0 || live1 > kFoldMaxWidth) continue;
-        int kw = 32;
-        while (kw < live1) kw *= 2;
+        int kw = 0;
+        for (int w : kFoldWidths)
+            if (kw < live1 || kw == 0) kw = w;
         FoldBuild b{};
         int wide = 0;
         FoldRun &R = b.run;
         if (!fold_scale(net, c.maxe, b.f, R.halvings, wide, R.vlo, R.vhi)) continue;
-        R.mt2 = L == 3 ? (live2 + 15) / 16 : 0;
-        R.stage_bytes = fold_stage_bytes(L, kw, R.mt2, two);
+        R.npair = L == 3 ? (live2 + 31) / 32 : 0;
+        R.stage_bytes = fold_stage_bytes(L, kw, R.npair, two);
         if (R.stage_bytes > kFoldMaxStage) continue;
-        if (net->forced_variant != kFoldVariantName && !fold_pays(q, kw, R.mt2)) continue;
+        if (net->forced_variant != kFoldVariantName && !fold_pays(q, kw, R.npair)) continue;
         const size_t o_v0 = bytes + al((size_t)q.dims[0] * kw * 2);
         const size_t o_et = o_v0 + al((size_t)kw * 4);
         const size_t o_st = o_et + al((size_t)q.dims[0] * props[c.pid].n_deltas * 2);
@@ -476,7 +482,7 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
         b.live2 = live2;
         b.epi = L == 3 && net->shift[1] == 7 ? 1 : 0;
         b.ws = fps[i].ws;
-        R.kbo = L == 3 ? (R.mt2 + 3) / 4 : 1;
+        R.free_pairs = b.epi ? live[4 * i + 1] >> 16 : 0;
         R.two = two;
         R.s2 = L == 3 ? net->shift[1] + 1 : 0;
         R.label = live[4 * i + 3];

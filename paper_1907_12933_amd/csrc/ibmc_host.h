@@ -135,6 +135,7 @@ struct ibmc_mlp {
     ibmc::FNetDev fd;
     ibmc::LaneNetDev lane{};           // integer nets the lane kernels serve (lane.ok)
     bool fold_ok = false;              // integer nets whose properties may be folded
+    bool fold_joint = false;           // their first two layers hold no weight of -128
     std::string forced_variant;
     ~ibmc_mlp();
 };

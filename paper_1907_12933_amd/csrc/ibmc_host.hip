@@ -363,6 +363,9 @@ static ibmc_status build_q8(ibmc_ctx *ctx, ibmc_mlp *m) {
     // layers' doubled inputs, folded biases and logit differences (each at
     // most 8 times |b| + 256 sum |w|)
     m->fold_ok = (L == 2 || L == 3) && m->dims[L] <= 16 && m->shift[0] <= 8;
+    m->fold_joint = true;
+    for (int l = 0; l < std::min(L, 2); ++l)
+        for (int8_t w : m->Wq[l]) m->fold_joint = m->fold_joint && w != -128;
     for (int l = 2; l <= L && m->fold_ok; ++l)
         for (int j = 0; j < m->dims[l] && m->fold_ok; ++j) {
             int64_t sa = 0;

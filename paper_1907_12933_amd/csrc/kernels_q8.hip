@@ -257,11 +257,59 @@ __global__ void __launch_bounds__(kCleanThreads) clean_q8_kernel(QNetDev net, Pr
 // can make (every delta between the smallest and the largest, clamped to
 // [0, 255] with the pixel).  k of them bound the potential over the whole
 // domain; the block that completes a property's slices turns the bounds into
-// activation intervals, carries them through the second hidden layer, and
-// writes the live units (interval of more than one value), the biases with
-// the constant units folded in, and the counts.  Latency-bound: one weight
-// pass over the first layer (as the clean pass) and one over the later ones.
+// activation intervals and lists the live units (intervals of more than one
+// value).  Latency-bound: one weight pass over the first layer (as the clean
+// pass) and the clean label's forward pass.
 constexpr int kScanSlice = 64;
+
+// Appends value to list for every thread of the block whose flag is set, in
+// thread order; returns how many (cnt: one int per wave).
+__device__ int fold_compact(bool flag, int value, int32_t *list, int *cnt) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const unsigned long long m = __ballot(flag);
+    if (lane == 0) cnt[wv] = __popcll(m);
+    __syncthreads();
+    int before = 0, all = 0;
+    for (int t = 0; t < nw; ++t) {
+        before += t < wv ? cnt[t] : 0;
+        all += cnt[t];
+    }
+    if (flag) list[before + __popcll(m & ((1ull << lane) - 1ull))] = value;
+    __syncthreads();
+    return all;
+}
+
+// Output layer of a folded property, a wave per row: bias with the constant
+// inputs, and the live inputs' weights times their offsets; then whether a
+// weight difference to the label's row leaves int8 on a live input.  iv(i):
+// input i's interval as lowest | highest << 8; off(i): its offset.
+template <class IV, class OFF>
+__device__ void fold_output(const QNetDev &net, int lab, int32_t *bo, int32_t *rso, int *two, IV iv, OFF off) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    const int L = net.L, nin = net.dims[L - 1], nc = net.dims[L];
+    for (int r = wv; r < nc; r += nw) {
+        const int8_t *row = net.Wd[L] + (int64_t)r * nin, *lrow = net.Wd[L] + (int64_t)lab * nin;
+        int cs = 0, sum = 0, wide = 0;
+#pragma unroll 4
+        for (int i = lane; i < nin; i += 64) {
+            const int c = row[i], d = c - (int)lrow[i], v = iv(i), a = v & 0xff;
+            const bool fixed = a == ((v >> 8) & 0xff);
+            cs += fixed ? c * a : 0;
+            sum += fixed ? 0 : c * off(i);
+            wide |= !fixed && (d < -128 || d > 127);
+        }
+        for (int d = 32; d > 0; d >>= 1) {
+            cs += __shfl_xor(cs, d);
+            sum += __shfl_xor(sum, d);
+        }
+        if (__ballot(wide) && lane == 0) *two = 1;
+        if (lane == 0) {
+            bo[r] = net.bd[L][r] + cs;
+            rso[r] = sum;
+        }
+    }
+    __syncthreads();
+}
 
 __global__ void __launch_bounds__(kCleanThreads) fold_scan_kernel(const QNetDev *nets, const FoldProp *fps,
                                                                   PropDev *props, const int32_t *block_map,
@@ -270,7 +318,7 @@ __global__ void __launch_bounds__(kCleanThreads) fold_scan_kernel(const QNetDev 
     __shared__ int part[3 * 64][kScanSlice];
     static_assert(sizeof(part) >= sizeof(int) * kFwdSplit * kMaxWidth, "dense tail scratch");
     __shared__ int lab, tie, last, cnt[16], two;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
     const FoldProp F = fps[block_map[blockIdx.x] >> 8];
     const int w = block_map[blockIdx.x] & 0xff;
     const QNetDev &net = nets[F.net];
@@ -326,37 +374,8 @@ __global__ void __launch_bounds__(kCleanThreads) fold_scan_kernel(const QNetDev 
     __syncthreads();
     if (!last) return;
     __threadfence();
-    for (int q = tid; q < H1; q += blockDim.x) {
-        const int neuron = sigma64(q);
-        if (neuron < h1) a0[neuron] = requant_relu(u0s[q], net.shift[0]);
-    }
-    __syncthreads();
-    dense_tail_block(net, a0, a1, reinterpret_cast<int (*)[kMaxWidth]>(&part[0][0]), nullptr, &lab, &tie);
-    __syncthreads();
-    if (tid == 0) {
-        props[F.pid].label0 = lab;
-        props[F.pid].tie0 = tie;
-        two = 0;
-    }
-    int *const alo = a0, *const ahi = a1;            // activation intervals, natural order
-    int *const blo = &part[0][0], *const bhi = blo + kMaxWidth;   // of the second hidden layer
-
-    // appends the indices whose flag is set to list, in index order; returns
-    // their number
-    auto compact = [&](bool flag, int value, int32_t *list) -> int {
-        const unsigned long long m = __ballot(flag);
-        if (lane == 0) cnt[wv] = __popcll(m);
-        __syncthreads();
-        int before = 0, all = 0;
-        for (int t = 0; t < 16; ++t) {
-            before += t < wv ? cnt[t] : 0;
-            all += cnt[t];
-        }
-        if (flag) list[before + __popcll(m & ((1ull << lane) - 1ull))] = value;
-        __syncthreads();
-        return all;
-    };
-    // layer 1 (H1 <= 1024 threads): 64-bit bounds, they may leave int32
+    // intervals of layer 1 (H1 <= 1024 threads): 64-bit bounds, they may
+    // leave int32
     bool live = false;
     if (tid < H1) {
         const int neuron = sigma64(tid);
@@ -365,74 +384,254 @@ __global__ void __launch_bounds__(kCleanThreads) fold_scan_kernel(const QNetDev 
             const int64_t hi = (u + (int64_t)F.k * F.ws[ws.ub + tid]) >> net.shift[0];
             const int64_t lo = (u + (int64_t)F.k * F.ws[ws.lb + tid]) >> net.shift[0];
             const int ih = (int)min((int64_t)127, max((int64_t)0, hi)), il = (int)min((int64_t)127, max((int64_t)0, lo));
-            ahi[neuron] = ih;
-            alo[neuron] = il;
+            const int a = requant_relu((int)u, net.shift[0]);
+            a0[neuron] = a;
+            F.ws[ws.iv1 + neuron] = il | ih << 8 | a << 16;
             live = ih != il;
         }
     }
-    const int live1 = compact(live, tid, F.ws + ws.list1);
-    // one later layer's rows: bias with the constant inputs, sum of the live
-    // inputs' weights, and (hidden) the potential's interval; a wave per row
-    auto rows = [&](int l, int nin, int nout, const int *il, const int *ih, int32_t *bf, int32_t *rs, int *ol,
-                    int *oh) {
-        for (int r = wv; r < nout; r += 16) {
-            const int8_t *row = net.Wd[l] + (int64_t)r * nin;
-            int cs = 0, sum = 0, lo = 0, hi = 0;
-            for (int i = lane; i < nin; i += 64) {
-                const int c = row[i], a = il[i], b = ih[i];
-                if (a == b) {
-                    cs += c * a;
-                } else {
-                    sum += c;
-                    lo += min(c * a, c * b);
-                    hi += max(c * a, c * b);
-                }
-            }
-            for (int d = 32; d > 0; d >>= 1) {
-                cs += __shfl_xor(cs, d);
-                sum += __shfl_xor(sum, d);
-                lo += __shfl_xor(lo, d);
-                hi += __shfl_xor(hi, d);
-            }
-            if (lane == 0) {
-                const int b = net.bd[l][r] + cs;
-                bf[r] = b;
-                rs[r] = sum;
-                if (ol) {
-                    ol[r] = requant_relu(b + lo, net.shift[l - 1]);
-                    oh[r] = requant_relu(b + hi, net.shift[l - 1]);
-                }
-            }
-        }
-        __syncthreads();
-    };
-    int live2 = 0;
-    if (L == 3) {
-        const int h2 = net.dims[2];
-        rows(2, h1, h2, alo, ahi, F.ws + ws.b2, F.ws + ws.rs2, blo, bhi);
-        live2 = compact(tid < h2 && blo[tid < h2 ? tid : 0] != bhi[tid < h2 ? tid : 0], tid, F.ws + ws.list2);
-        rows(3, h2, net.dims[3], blo, bhi, F.ws + ws.bo, F.ws + ws.rso, nullptr, nullptr);
-    } else {
-        rows(2, h1, net.dims[2], alo, ahi, F.ws + ws.bo, F.ws + ws.rso, nullptr, nullptr);
-    }
-    // does a weight difference to the label's row leave int8 on a live input?
-    const int hl = net.dims[L - 1], nc = net.dims[L];
-    const int *il = L == 3 ? blo : alo, *ih = L == 3 ? bhi : ahi;
-    bool wide = false;
-    for (int t = tid; t < nc * hl; t += blockDim.x) {
-        const int i = t % hl;
-        if (il[i] != ih[i]) {
-            const int d = (int)net.Wd[L][t] - (int)net.Wd[L][(int64_t)lab * hl + i];
-            wide |= d < -128 || d > 127;
-        }
-    }
-    if (wide) two = 1;
+    const int live1 = fold_compact(live, tid, F.ws + ws.list1, cnt);
+    dense_tail_block(net, a0, a1, reinterpret_cast<int (*)[kMaxWidth]>(&part[0][0]), nullptr, &lab, &tie);
     __syncthreads();
     if (tid == 0) {
+        props[F.pid].label0 = lab;
+        props[F.pid].tie0 = tie;
+        F.ws[ws.done] = 0;
         F.counts[0] = live1;
-        F.counts[1] = live2;
-        F.counts[2] = two;
         F.counts[3] = lab;
+        two = 0;
+    }
+    __syncthreads();
+    if (L == 2) {
+        fold_output(net, lab, F.ws + ws.bo, F.ws + ws.rso, &two, [&](int i) { return F.ws[ws.iv1 + i]; },
+                    [](int) { return 64; });
+        if (tid == 0) {
+            F.counts[1] = 0;
+            F.counts[2] = two;
+        }
+    }
+}
+
+// Second hidden layer of the scanned three-layer properties.  A block takes
+// 64 rows of one property: per row the bias with the constant inputs, the
+// live weights' sum, and bounds of the potential over the domain, the
+// tighter of
+//   - the inputs' intervals, and
+//   - the joint bound: one pixel's change d of the first-layer potentials
+//     moves the row by at most sum_j max(0, w_j d_j) / 2^s (the requantiser is
+//     monotone and contracts by 2^s), and with d_j = e W_jp
+//     sum_j max(0, w_j W_jp) = (sum |w_j| |W_jp| + sum w_j W_jp) / 2: two int8
+//     matrix products over the pixels.  k times the largest over the pixels,
+//     plus the live weights' |w| for the floors.
+// On blob images with k = 2 it leaves about two thirds of the units that the
+// intervals alone leave live, and half of the ones with both ends in reach.
+// The block that completes a property lists the live rows in the order of
+// their forms (FoldForm) and does the output layer.
+constexpr int kBoundPix = 256;   // pixels per round of the joint bound
+
+__global__ void __launch_bounds__(256) fold_bound_kernel(const QNetDev *nets, const FoldProp *fps, const PropDev *props,
+                                                         const int32_t *row_map) {
+    __shared__ __attribute__((aligned(16))) int8_t wb[kBoundPix / 16 * 1024];   // one K-block of pixel columns
+    __shared__ int l1[kFoldMaxWidth];
+    __shared__ int res[64][6];
+    __shared__ int cnt[4], last, two;
+    __shared__ int iv2[kMaxWidth];
+    __shared__ int16_t offs[kMaxWidth];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int j16 = lane & 15, g = lane >> 4;
+    const FoldProp F = fps[row_map[blockIdx.x] >> 8];
+    const int r0 = (row_map[blockIdx.x] & 0xff) * 64;
+    const QNetDev &net = nets[F.net];
+    const int n = net.dims[0], H1 = net.H[1], h1 = net.dims[1], h2 = net.dims[2];
+    const FoldWs ws = fold_ws(H1, net.H[2]);
+    const int live1 = F.counts[0];
+    const int8_t *W2 = net.Wd[2];
+    // row sums, a row per lane and a quarter of the columns per wave: constant
+    // part, live weights, interval below and above the constant part, live
+    // |w|, live clean part
+    for (int t = tid; t < kMaxWidth; t += 256) iv2[t] = t < h1 ? F.ws[ws.iv1 + t] : 0;
+    for (int t = tid; t < kFoldMaxWidth; t += 256) l1[t] = t < live1 ? F.ws[ws.list1 + t] : -1;
+    for (int t = tid; t < 64 * 6; t += 256) (&res[0][0])[t] = 0;
+    __syncthreads();
+    {
+        const int row = min(r0 + lane, h2 - 1);
+        const int8_t *wr = W2 + (int64_t)row * h1;
+        const int per = ((h1 + 15) / 16) * 4, c0 = wv * per, c1 = min(c0 + per, h1);   // columns, in fours
+        const bool words = h1 % 4 == 0;
+        int v[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll 4
+        for (int i = c0; i < c1; i += 4) {
+            unsigned wd = 0;
+            if (words) {
+                wd = *reinterpret_cast<const unsigned *>(wr + i);
+            } else {
+#pragma unroll
+                for (int z = 0; z < 4; ++z) wd |= (unsigned)(uint8_t)wr[min(i + z, h1 - 1)] << (8 * z);
+            }
+#pragma unroll
+            for (int z = 0; z < 4; ++z) {
+                // (past the end: interval 0..0)
+                const int iv = iv2[i + z], lo = iv & 0xff, hi = (iv >> 8) & 0xff, a = iv >> 16;
+                const int c = (int)(int8_t)(wd >> (8 * z));
+                const bool live = lo != hi;
+                v[0] += live ? 0 : c * lo;
+                v[1] += live ? c : 0;
+                v[2] += live ? min(c * lo, c * hi) : 0;
+                v[3] += live ? max(c * lo, c * hi) : 0;
+                v[4] += live ? abs(c) : 0;
+                v[5] += live ? c * a : 0;
+            }
+        }
+#pragma unroll
+        for (int z = 0; z < 6; ++z) atomicAdd(&res[lane][z], v[z]);
+    }
+    __syncthreads();
+    // joint bound of the wave's 16 rows: lane (j16, g) holds rows 4 g + z
+    const bool joint = F.joint && live1 > 0 && live1 <= kFoldMaxWidth;
+    int mu[4] = {0, 0, 0, 0}, md[4] = {0, 0, 0, 0};
+    if (joint) {
+        const uint8_t *x = props[F.pid].image;
+        const int KB = (live1 + 63) / 64;
+        for (int p0 = 0; p0 < n; p0 += kBoundPix) {
+            v4i sp[kBoundPix / 16], sq[kBoundPix / 16];   // sum w W and sum |w| |W| per pixel tile
+#pragma unroll
+            for (int t = 0; t < kBoundPix / 16; ++t) sp[t] = sq[t] = v4i{0, 0, 0, 0};
+            for (int kb = 0; kb < KB; ++kb) {
+                __syncthreads();
+                // this K-block's columns of the pixels: thread (pixel tid / 16 + 16 r,
+                // dword tid % 16), every byte load of eight pixels in flight together
+                {
+                    const int ln = tid & 15, px = tid >> 4;      // dword (ln / 4 = lane group, ln % 4)
+                    int q[4];
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) q[z] = l1[kb * 64 + ln * 4 + z];
+                    for (int r = 0; r < kBoundPix / 16; r += 8) {
+                        unsigned v[8];
+#pragma unroll
+                        for (int h = 0; h < 8; ++h) {
+                            const int p = p0 + (r + h) * 16 + px;
+                            const int8_t *col = net.W1T + (int64_t)min(p, n - 1) * H1;
+                            v[h] = 0;
+#pragma unroll
+                            for (int z = 0; z < 4; ++z) {
+                                const unsigned c = (unsigned)(uint8_t)col[max(q[z], 0)];
+                                v[h] |= (q[z] >= 0 ? c : 0u) << (8 * z);
+                            }
+                            if (p >= n) v[h] = 0;
+                        }
+#pragma unroll
+                        for (int h = 0; h < 8; ++h)   // tile r + h, lane px + 16 (ln / 4), dword ln % 4
+                            reinterpret_cast<unsigned *>(wb)[(r + h) * 256 + (px + 16 * (ln >> 2)) * 4 + (ln & 3)] = v[h];
+                    }
+                }
+                v4i A, B;
+                const int row = r0 + wv * 16 + j16;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    unsigned v = 0, u = 0;
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) {
+                        const int q = l1[kb * 64 + g * 16 + d * 4 + z];
+                        const int w = (int)W2[(int64_t)min(row, h2 - 1) * h1 + (q >= 0 ? sigma64(q) : 0)];
+                        const int c = row < h2 && q >= 0 ? w : 0;
+                        v |= (unsigned)(uint8_t)c << (8 * z);
+                        u |= (unsigned)abs(c) << (8 * z);
+                    }
+                    A[d] = (int)v;
+                    B[d] = (int)u;
+                }
+                __syncthreads();
+#pragma unroll
+                for (int t = 0; t < kBoundPix / 16; ++t) {
+                    const v4i W = *reinterpret_cast<const v4i *>(wb + t * 1024 + lane * 16);
+                    v4i N;
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) {
+                        // |byte| = (byte ^ s) - s with s = -1 for negative bytes, no borrow between bytes
+                        const unsigned s = (((unsigned)W[d] >> 7) & 0x01010101u);
+                        N[d] = (int)(((unsigned)W[d] ^ (s * 0xffu)) + s);
+                    }
+                    sp[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, W, sp[t], 0, 0, 0);
+                    sq[t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(B, N, sq[t], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < kBoundPix / 16; ++t) {
+                const int p = p0 + t * 16 + j16;
+                const int xv = p < n ? x[p] : 0;
+                const int eh = p < n ? min(xv + F.dhi, 255) - xv : 0, el = p < n ? xv - max(xv + F.dlo, 0) : 0;
+#pragma unroll
+                for (int z = 0; z < 4; ++z) {
+                    const int pos = (sq[t][z] + sp[t][z]) >> 1, neg = (sq[t][z] - sp[t][z]) >> 1;
+                    // (24-bit products: pos, neg < 2^23)
+                    mu[z] = max(mu[z], max(__mul24(pos, eh), __mul24(neg, el)));
+                    md[z] = max(md[z], max(__mul24(neg, eh), __mul24(pos, el)));
+                }
+            }
+        }
+        for (int d = 8; d > 0; d >>= 1)
+#pragma unroll
+            for (int z = 0; z < 4; ++z) {
+                mu[z] = max(mu[z], __shfl_xor(mu[z], d));
+                md[z] = max(md[z], __shfl_xor(md[z], d));
+            }
+    }
+    if (j16 < 4) {
+        const int lr = wv * 16 + 4 * g + j16, row = r0 + lr;
+        const int up = j16 == 0 ? mu[0] : j16 == 1 ? mu[1] : j16 == 2 ? mu[2] : mu[3];
+        const int dn = j16 == 0 ? md[0] : j16 == 1 ? md[1] : j16 == 2 ? md[2] : md[3];
+        if (row < h2) {
+            const int b = net.bd[2][row] + res[lr][0];
+            int64_t lo = (int64_t)b + res[lr][2], hi = (int64_t)b + res[lr][3];
+            if (joint) {
+                const int64_t c = (int64_t)b + res[lr][5];
+                hi = min(hi, c + res[lr][4] + 1 + ((int64_t)F.k * up >> net.shift[0]));
+                lo = max(lo, c - res[lr][4] - 1 - ((int64_t)F.k * dn >> net.shift[0]));
+            }
+            const int s2 = net.shift[1];
+            const int form = lo >= 0 ? FOLD_UPPER : (hi >> s2) <= 127 ? FOLD_LOWER : FOLD_BOTH;
+            const int al = (int)min((int64_t)127, max((int64_t)0, lo >> s2));
+            const int ah = (int)min((int64_t)127, max((int64_t)0, hi >> s2));
+            F.ws[ws.b2 + row] = b;
+            F.ws[ws.rs2 + row] = res[lr][1];
+            F.ws[ws.iv2 + row] = al | ah << 8 | form << 16;
+        }
+    }
+    __threadfence();
+    __syncthreads();
+    if (tid == 0) last = atomicAdd(&F.ws[ws.done], 1) + 1 == (h2 + 63) / 64;
+    __syncthreads();
+    if (!last) return;
+    __threadfence();
+    // live rows by form; with the saturating epilogue (shift 7) the pairs of
+    // tiles that hold no row with both ends in reach need no cap, and their FOLD_UPPER
+    // rows take offset 0 instead of 128
+    const bool sat = net.shift[1] == 7;
+    for (int t = tid; t < h2; t += 256) iv2[t] = F.ws[ws.iv2 + t];
+    if (tid == 0) two = 0;
+    __syncthreads();
+    int total = 0, n_free = 0;
+    for (int f = FOLD_UPPER; f <= FOLD_BOTH; ++f) {
+        for (int b = 0; b < h2; b += 256) {
+            const int row = b + tid;
+            const int iv = row < h2 ? iv2[row] : 0;
+            const bool on = row < h2 && (iv & 0xff) != ((iv >> 8) & 0xff) && (iv >> 16) == f;
+            total += fold_compact(on, row, F.ws + ws.list2 + total, cnt);
+        }
+        if (f <= FOLD_LOWER) n_free = total;
+    }
+    // (with every live row free of the cap, the last, partly filled pair is too)
+    const int free_pairs = !sat ? 0 : n_free == total ? (total + 31) / 32 : n_free / 32;
+    for (int t = tid; t < total; t += 256) {
+        const int row = F.ws[ws.list2 + t];
+        offs[row] = (int16_t)(!sat ? 64 : t / 32 < free_pairs && (iv2[row] >> 16) == FOLD_UPPER ? 0 : 128);
+    }
+    __syncthreads();
+    fold_output(net, F.counts[3], F.ws + ws.bo, F.ws + ws.rso, &two, [&](int i) { return iv2[i]; },
+                [&](int i) { return (int)offs[i]; });
+    if (tid == 0) {
+        F.counts[1] = total | free_pairs << 16;
+        F.counts[2] = two;
     }
 }
 
@@ -534,6 +733,13 @@ hipError_t launch_fold_scan(const QNetDev *nets, const FoldProp *fps, PropDev *p
     if (n_blocks <= 0) return hipSuccess;
     hipLaunchKernelGGL(fold_scan_kernel, dim3(n_blocks), dim3(kCleanThreads), 0, s, nets, fps, props, block_map,
                        u0_store, u0_stride);
+    return hipGetLastError();
+}
+
+hipError_t launch_fold_bound(const QNetDev *nets, const FoldProp *fps, const PropDev *props, const int32_t *row_map,
+                             int n_blocks, hipStream_t s) {
+    if (n_blocks <= 0) return hipSuccess;
+    hipLaunchKernelGGL(fold_bound_kernel, dim3(n_blocks), dim3(256), 0, s, nets, fps, props, row_map);
     return hipGetLastError();
 }
 
