@@ -19,9 +19,10 @@ using namespace ibmc;
 
 namespace {
 
-// Workgroups whose partial rows one launch may hold (256 MiB at most).
-int64_t tiles_cap(int64_t n_params) {
-    return std::max<int64_t>(1, std::min<int64_t>(4096, (256ll << 20) / (4 * n_params)));
+// Samples of one pass at most: its rows of activations and deltas take up to
+// 256 MiB.
+int64_t pass_cap(const TrainNetDev &N) {
+    return std::max<int64_t>(kTrainTile, (256ll << 20) / (8ll * N.units) / kTrainTile * kTrainTile);
 }
 
 ibmc_status check_train_args(ibmc_ctx *ctx, const ibmc_mlp *net, const uint8_t *images, const int32_t *labels,
@@ -63,39 +64,14 @@ void shuffle_epoch(uint64_t seed, int epoch, std::vector<int64_t> &ord) {
     }
 }
 
-// grad (+)= the gradient sum of elements e0 .. e0 + count - 1 of the pass,
-// split into launches of at most tiles_cap workgroups; loss_acc += their loss.
-ibmc_status grad_pass(const TrainNetDev &N, const float *theta, const uint8_t *images, const int32_t *labels,
-                      const int64_t *order, int64_t e0, int64_t count, int tile, float inv_n, DevBuf &partial,
-                      DevBuf &partial_loss, float *grad, bool accumulate, double *loss_acc, hipStream_t s) {
-    const int64_t cap = tiles_cap(N.n_params);
-    for (int64_t done = 0; done < count;) {
-        const int64_t c = std::min<int64_t>(count - done, cap * tile);
-        TrainGradParams P;
-        P.net = N;
-        P.theta = theta;
-        P.images = images;
-        P.labels = labels;
-        P.order = order;
-        P.e0 = e0 + done;
-        P.count = c;
-        P.tile = tile;
-        P.inv_n = inv_n;
-        P.partial = partial.as<float>();
-        P.partial_loss = partial_loss.as<float>();
-        HIP_OK(launch_train_grad(P, s));
-        const int tiles = (int)((c + tile - 1) / tile);
-        HIP_OK(launch_train_reduce(P.partial, P.partial_loss, tiles, N.n_params, grad, accumulate || done > 0,
-                                   loss_acc, s));
-        done += c;
-    }
-    return IBMC_OK;
-}
-
-ibmc_status reserve_partials(const TrainNetDev &N, int64_t count, int tile, DevBuf &partial, DevBuf &partial_loss) {
-    const int64_t tiles = std::min<int64_t>(tiles_cap(N.n_params), (count + tile - 1) / tile);
-    IBMC_TRY(partial.reserve((size_t)tiles * N.n_params * 4));
-    IBMC_TRY(partial_loss.reserve((size_t)tiles * 4));
+// Buffers of passes of up to `count` samples, carved from one allocation.
+ibmc_status reserve_pass(const TrainNetDev &N, int64_t count, DevBuf &buf, TrainPassParams &P) {
+    const int64_t rows = (std::min(count, pass_cap(N)) + kTrainTile - 1) / kTrainTile * kTrainTile;
+    IBMC_TRY(buf.reserve((size_t)(2 * rows * N.units + rows / kTrainTile) * sizeof(float)));
+    P.net = N;
+    P.acts = buf.as<float>();
+    P.dels = P.acts + rows * N.units;
+    P.loss = P.dels + rows * N.units;
     return IBMC_OK;
 }
 
@@ -110,17 +86,28 @@ extern "C" ibmc_status ibmc_mlp_loss_grad(ibmc_ctx *ctx, const ibmc_mlp *net, co
     hipStream_t s = ctx->stream;
     const TrainNetDev N = train_layout(net->L, net->dims.data());
     const std::vector<float> th = flat_theta(net);
-    const int tile = train_tile(N, kTrainMaxTile);
-    DevBuf dth, dimg, dlab, dgrad, part, ploss, dloss;
+    DevBuf dth, dimg, dlab, dgrad, rows, dloss;
+    TrainPassParams P{};
     IBMC_TRY(dth.upload(th.data(), th.size() * 4, s));
     IBMC_TRY(dimg.upload(images, (size_t)n * net->dims[0], s));
     IBMC_TRY(dlab.upload(labels, (size_t)n * 4, s));
     IBMC_TRY(dgrad.reserve((size_t)N.n_params * 4));
     IBMC_TRY(dloss.reserve(8));
-    IBMC_TRY(reserve_partials(N, n, tile, part, ploss));
+    IBMC_TRY(reserve_pass(N, n, rows, P));
     HIP_OK(launch_fill_u64(dloss.as<unsigned long long>(), 1, 0ull, s));
-    IBMC_TRY(grad_pass(N, dth.as<float>(), dimg.as<uint8_t>(), dlab.as<int32_t>(), nullptr, 0, n, tile,
-                       (float)(1.0 / (double)n), part, ploss, dgrad.as<float>(), false, dloss.as<double>(), s));
+    P.theta = dth.as<float>();
+    P.images = dimg.as<uint8_t>();
+    P.labels = dlab.as<int32_t>();
+    P.inv_n = (float)(1.0 / (double)n);
+    TrainUpdate U{};
+    U.grad = dgrad.as<float>();
+    U.loss_acc = dloss.as<double>();
+    for (P.e0 = 0; P.e0 < n; P.e0 += P.count) {
+        P.count = std::min<int64_t>(n - P.e0, pass_cap(N));
+        U.accumulate = P.e0 > 0;
+        HIP_OK(launch_train_pass(P, s));
+        HIP_OK(launch_train_weights(P, U, s));
+    }
     double l = 0.0;
     HIP_OK(hipMemcpyAsync(&l, dloss.p, 8, hipMemcpyDeviceToHost, s));
     if (grad) HIP_OK(hipMemcpyAsync(grad, dgrad.p, (size_t)N.n_params * 4, hipMemcpyDeviceToHost, s));
@@ -150,21 +137,35 @@ extern "C" ibmc_status ibmc_fit_mlp(ibmc_ctx *ctx, const ibmc_mlp *net, const ui
     hipStream_t s = ctx->stream;
     const TrainNetDev N = train_layout(net->L, net->dims.data());
     const int64_t B = std::min<int64_t>(o->batch, n);
-    const int tile = train_tile(N, (int)std::min<int64_t>(kTrainMaxTile, (B + 31) / 32));
     std::vector<float> th = flat_theta(net);
-    DevBuf dth, dmom, dvel, dgrad, dimg, dlab, dord, part, ploss, dloss;
+    DevBuf dth, dmom, dvel, dgrad, dimg, dlab, dord, rows, dloss;
+    TrainPassParams P{};
     IBMC_TRY(dth.upload(th.data(), th.size() * 4, s));
-    IBMC_TRY(dmom.reserve((size_t)N.n_params * 4));
-    IBMC_TRY(dvel.reserve((size_t)N.n_params * 4));
-    IBMC_TRY(dgrad.reserve((size_t)N.n_params * 4));
+    IBMC_TRY(dmom.reserve((size_t)N.n_params * 4 + 4));
+    IBMC_TRY(dvel.reserve((size_t)N.n_params * 4 + 4));
     IBMC_TRY(dimg.upload(images, (size_t)n * net->dims[0], s));
     IBMC_TRY(dlab.upload(labels, (size_t)n * 4, s));
     IBMC_TRY(dord.reserve((size_t)n * 8));
     IBMC_TRY(dloss.reserve((size_t)o->epochs * 8));
-    IBMC_TRY(reserve_partials(N, B, tile, part, ploss));
+    IBMC_TRY(reserve_pass(N, B, rows, P));
+    // a batch beyond one pass gathers its gradient before its step
+    const bool whole = B <= pass_cap(N);
+    if (!whole) IBMC_TRY(dgrad.reserve((size_t)N.n_params * 4));
     HIP_OK(launch_fill_u64(dmom.as<unsigned long long>(), (N.n_params + 1) / 2, 0ull, s));
     HIP_OK(launch_fill_u64(dvel.as<unsigned long long>(), (N.n_params + 1) / 2, 0ull, s));
     HIP_OK(launch_fill_u64(dloss.as<unsigned long long>(), o->epochs, 0ull, s));
+    P.theta = dth.as<float>();
+    P.images = dimg.as<uint8_t>();
+    P.labels = dlab.as<int32_t>();
+    P.order = dord.as<int64_t>();
+    TrainUpdate U{};
+    U.theta = dth.as<float>();
+    U.mom = dmom.as<float>();
+    U.vel = dvel.as<float>();
+    U.lr = o->lr;
+    U.b1 = b1;
+    U.b2 = b2;
+    U.eps = eps;
     std::vector<int64_t> ord(n);
     int64_t step = 0;
     for (int ep = 0; ep < o->epochs; ++ep) {
@@ -175,14 +176,28 @@ extern "C" ibmc_status ibmc_fit_mlp(ibmc_ctx *ctx, const ibmc_mlp *net, const ui
         HIP_OK(hipMemcpyAsync(dord.p, ord.data(), (size_t)n * 8, hipMemcpyHostToDevice, s));
         for (int64_t b0 = 0; b0 < n; b0 += B) {
             const int64_t cnt = std::min<int64_t>(B, n - b0);
-            IBMC_TRY(grad_pass(N, dth.as<float>(), dimg.as<uint8_t>(), dlab.as<int32_t>(), dord.as<int64_t>(), b0,
-                               cnt, tile, (float)(1.0 / (double)cnt), part, ploss, dgrad.as<float>(), false,
-                               dloss.as<double>() + ep, s));
             ++step;
-            const float c1 = (float)(1.0 - std::pow((double)b1, (double)step));
-            const float c2 = (float)(1.0 - std::pow((double)b2, (double)step));
+            U.c1 = (float)(1.0 - std::pow((double)b1, (double)step));
+            U.c2 = (float)(1.0 - std::pow((double)b2, (double)step));
+            U.loss_acc = dloss.as<double>() + ep;
+            P.inv_n = (float)(1.0 / (double)cnt);
+            P.e0 = b0;
+            P.count = cnt;
+            if (whole) {
+                HIP_OK(launch_train_pass(P, s));
+                HIP_OK(launch_train_weights(P, U, s));
+                continue;
+            }
+            TrainUpdate G = U;
+            G.grad = dgrad.as<float>();
+            for (; P.e0 < b0 + cnt; P.e0 += P.count) {
+                P.count = std::min<int64_t>(b0 + cnt - P.e0, pass_cap(N));
+                G.accumulate = P.e0 > b0;
+                HIP_OK(launch_train_pass(P, s));
+                HIP_OK(launch_train_weights(P, G, s));
+            }
             HIP_OK(launch_prop_adam(dth.as<float>(), dgrad.as<float>(), dmom.as<float>(), dvel.as<float>(),
-                                    (int)N.n_params, o->lr, b1, b2, eps, c1, c2, s));
+                                    (int)N.n_params, o->lr, b1, b2, eps, U.c1, U.c2, s));
         }
         HIP_OK(hipStreamSynchronize(s));   // ord is rewritten next epoch
     }

@@ -10,8 +10,7 @@
 namespace ibmc {
 
 constexpr int kTrainThreads = 1024;
-constexpr int kTrainMaxTile = 16;          // samples per workgroup
-constexpr int kTrainLdsBytes = 64 * 1024;  // LDS of one workgroup
+constexpr int kTrainTile = 4;              // samples per workgroup of the pass
 
 // The flat parameter vector theta: for each layer l = 1..L in turn, W_l
 // row-major [dims[l]][dims[l-1]] then b_l [dims[l]].
@@ -20,35 +19,39 @@ struct TrainNetDev {
     int dims[kMaxLayers + 1];
     int64_t toff[kMaxLayers + 1];   // l >= 1: offset of W_l in theta (b_l follows it)
     int64_t n_params;
-    // per-sample LDS layout: activations a_0 .. a_L at aoff[l] (a_L = the
-    // logits), units = dims[0] + sum of the other widths; deltas dL/du of
-    // layers 1..L at aoff[l] - dims[0] in a block of units - dims[0]
+    // per-sample row of activations a_0 .. a_L (a_L = the logits) at aoff[l],
+    // each layer padded to four; deltas dL/du of layers 1..L in the same places
     int aoff[kMaxLayers + 1];
     int units;
+    int widest;                     // widest layer, padded to four
 };
 
 TrainNetDev train_layout(int L, const int *dims);
-// Samples per workgroup: wanted (>= 1) clipped to what LDS holds.
-int train_tile(const TrainNetDev &N, int wanted);
-size_t train_lds_bytes(const TrainNetDev &N, int tile);
 
-struct TrainGradParams {
+// One pass over elements e0 .. e0 + count - 1: rows of activations and deltas
+// (count padded to kTrainTile rows) and one loss sum per workgroup.
+struct TrainPassParams {
     TrainNetDev net;
     const float *theta;
     const uint8_t *images;     // [n_images][dims[0]]
     const int32_t *labels;     // [n_images], each in [0, dims[L])
     const int64_t *order;      // nullable: element e of the pass is image order[e]
-    int64_t e0, count;         // this launch: elements e0 .. e0 + count - 1
-    int tile;                  // samples per workgroup
+    int64_t e0, count;
     float inv_n;               // 1 / the number of samples the mean runs over
-    float *partial;            // [ceil(count / tile)][n_params] per-workgroup gradient sums
-    float *partial_loss;       // [ceil(count / tile)] per-workgroup loss sums
+    float *acts, *dels;        // [rows][units]
+    float *loss;               // [ceil(count / kTrainTile)]
 };
 
-hipError_t launch_train_grad(const TrainGradParams &P, hipStream_t s);
-// grad = (accumulate ? grad : 0) + the sum of the tiles' partials, in tile
-// order; *loss_acc += the sum of the tiles' loss sums (in order, double).
-hipError_t launch_train_reduce(const float *partial, const float *partial_loss, int tiles, int64_t n_params,
-                               float *grad, bool accumulate, double *loss_acc, hipStream_t s);
+// What becomes of the weight gradients of a pass.
+struct TrainUpdate {
+    float *grad;               // non-null: grad = (accumulate ? grad : 0) + gradient
+    int accumulate;
+    float *theta, *mom, *vel;  // grad null: one Adam step
+    float lr, b1, b2, eps, c1, c2;
+    double *loss_acc;          // += the pass's loss sum
+};
+
+hipError_t launch_train_pass(const TrainPassParams &P, hipStream_t s);
+hipError_t launch_train_weights(const TrainPassParams &P, const TrainUpdate &U, hipStream_t s);
 
 }  // namespace ibmc
