@@ -255,6 +255,11 @@ static const LaneInst *find_lane(const LaneNetDev &net) {
     return nullptr;
 }
 
+const void *lane_enum_kernel(const LaneNetDev &net) {
+    const LaneInst *v = net.ok ? find_lane(net) : nullptr;
+    return v ? v->fn : nullptr;
+}
+
 int lane_enum_grid(const LaneNetDev &net, int n_cu) {
     const LaneInst *v = net.ok ? find_lane(net) : nullptr;
     if (!v) return 0;

@@ -118,7 +118,20 @@ struct BatchState {
     std::vector<std::vector<int>> level_k;    // k per level per property
     std::vector<int> slot_base;               // first slot of each property
     int n_slots = 0;
+    bool ev1_ends = false;                    // no device work was queued after ev1's last record
+    // the call's inputs, [properties][images] in ctx->props and their pinned
+    // source: sent with the plan in one copy where the plan fits behind them
+    // (plan_room bytes from o_plan on), or earlier when a kernel needs them
+    char *host_in = nullptr;
+    size_t in_bytes = 0, o_plan = 0, plan_room = 0;
+    bool in_sent = false;
 };
+
+static ibmc_status send_inputs(ibmc_ctx *ctx, BatchState &B) {
+    if (!B.in_sent) HIP_OK(hipMemcpyAsync(ctx->props.p, B.host_in, B.in_bytes, hipMemcpyHostToDevice, ctx->stream));
+    B.in_sent = true;
+    return IBMC_OK;
+}
 
 // Digits per pixel side of the L2-ball domain: min(floor(sqrt(r2)), 255).
 static int ball_rd(int64_t r2) {
@@ -296,18 +309,14 @@ struct FoldBucket {
 // jobs (tens of milliseconds each).
 constexpr int64_t kFoldJobPoints = (int64_t)1 << 31;
 
-// What folding saves is worth its extra pass (scan, one read-back, gather:
-// about 60 us) from this much estimated enumeration time on.
-constexpr double kFoldMinSeconds = 150e-6;
+// What folding saves is worth its extra work (scan, one read-back, gather) from
+// this many points of a call on, a point of a three-layer network (whose scan
+// has a second kernel) counting kFoldPoint3.  Measured as whole calls with and
+// without folding: 35-16-5, 21,630 points 148 / 155 us, 64-32-10, 72,960 points
+// 149 / 165 us, 8,192 points 146 / 133 us; 196-128-64-10, 76,832 points 174 / 173
+// us, 48-200-150-10, 142,976 points 195 / 215 us, 40,896 points 197 / 162 us.
+constexpr double kFoldMinPoints = 30000, kFoldPoint3 = 0.35;
 constexpr size_t kFoldMaxBytes = (size_t)1 << 30;
-
-// Estimated seconds of the unfolded enumeration of one property (measured
-// rates of the matrix-core and the lane kernels on large workloads).
-static double unfolded_seconds(const ibmc_mlp *net, bool lane, int64_t points) {
-    int64_t macs = 0;
-    for (int l = 2; l <= net->L; ++l) macs += (int64_t)net->dims[l] * net->dims[l - 1];
-    return points * (lane ? 4e-12 : 12e-12 + 0.75e-15 * macs);
-}
 
 // The reduced network beats the instance the property would run on: fewer
 // matrix-core tiles per point in the hidden layers.
@@ -350,7 +359,7 @@ static bool fold_scale(const ibmc_mlp *net, int maxe, int &f, int &halvings, int
 // the L2 ball, a forced variant, the int32 testing aid, or when buffers come
 // from the fixed scratch array.
 static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, const ibmc_check_opts *o,
-                                   const BatchState &B, const std::vector<std::vector<int>> &level_sel, int64_t max_h1,
+                                   BatchState &B, const std::vector<std::vector<int>> &level_sel, int64_t max_h1,
                                    bool resumable, std::vector<NetPlan> &plans, std::vector<FoldBucket> &buckets) {
     if (resumable || o->property == IBMC_PROPERTY_LITERAL || ctx->force_int32_layer1 || thread_arena()) return IBMC_OK;
     hipStream_t s = ctx->stream;
@@ -368,7 +377,6 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
         if (net->act != IBMC_ACT_RELU_Q8 || !net->fold_ok) continue;
         const bool forced = net->forced_variant == kFoldVariantName;
         if (!forced && !net->forced_variant.empty()) continue;
-        const bool lane = use_lane(ctx, net, true);
         const size_t c0 = cands.size();
         bool any_ball = false;
         for (int pid : pl.ids) {
@@ -388,13 +396,13 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
             cands.resize(c0);
             continue;
         }
-        for (size_t i = c0; i < cands.size(); ++i) est += forced ? kFoldMinSeconds : unfolded_seconds(net, lane, cands[i].points);
+        for (size_t i = c0; i < cands.size(); ++i) est += forced ? kFoldMinPoints : cands[i].points * (net->L == 3 ? kFoldPoint3 : 1.0);
         ws_ints += pl.ids.size() * (size_t)fold_ws(net->qd.H[1], net->L == 3 ? net->qd.H[2] : 0).total;
         nets.push_back(net->qd);
         net_plan.push_back(&pl);
     }
     // (kFoldMaxJobs: the kernel's job search)
-    if (cands.empty() || est < kFoldMinSeconds || ws_ints * 4 > kFoldMaxBytes || n_jobs > kFoldMaxJobs) return IBMC_OK;
+    if (cands.empty() || est < kFoldMinPoints || ws_ints * 4 > kFoldMaxBytes || n_jobs > kFoldMaxJobs) return IBMC_OK;
 
     // scan: [networks][properties][block map] in, counts and lists out
     const size_t nc = cands.size();
@@ -426,19 +434,23 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
     const size_t o_fp = al(nets.size() * sizeof(QNetDev)), o_map = o_fp + al(nc * sizeof(FoldProp));
     const size_t n_scan = map.size();
     map.insert(map.end(), rmap.begin(), rmap.end());
-    std::vector<char> in(o_map + map.size() * 4);
-    memcpy(in.data(), nets.data(), nets.size() * sizeof(QNetDev));
-    memcpy(in.data() + o_fp, fps.data(), nc * sizeof(FoldProp));
-    memcpy(in.data() + o_map, map.data(), map.size() * 4);
-    IBMC_TRY(ctx->fold_in.upload(in.data(), in.size(), s));
+    void *in = nullptr;
+    IBMC_TRY(ctx->pin.take(o_map + map.size() * 4, &in));
+    memcpy(in, nets.data(), nets.size() * sizeof(QNetDev));
+    memcpy((char *)in + o_fp, fps.data(), nc * sizeof(FoldProp));
+    memcpy((char *)in + o_map, map.data(), map.size() * 4);
+    IBMC_TRY(ctx->fold_in.upload(in, o_map + map.size() * 4, s));
     const QNetDev *dnets = ctx->fold_in.as<QNetDev>();
     PropDev *dprops = ctx->props.as<PropDev>();
+    IBMC_TRY(send_inputs(ctx, B));
     const FoldProp *dfps = reinterpret_cast<const FoldProp *>(ctx->fold_in.as<char>() + o_fp);
     const int32_t *dmap = reinterpret_cast<const int32_t *>(ctx->fold_in.as<char>() + o_map);
     HIP_OK(launch_fold_scan(dnets, dfps, dprops, dmap, (int)n_scan, ctx->u0.as<int32_t>(), max_h1, s));
     HIP_OK(launch_fold_bound(dnets, dfps, dprops, dmap + n_scan, (int)rmap.size(), s));
-    std::vector<int32_t> live(4 * nc);
-    HIP_OK(hipMemcpyAsync(live.data(), counts, live.size() * 4, hipMemcpyDeviceToHost, s));
+    void *back = nullptr;
+    IBMC_TRY(ctx->pin.take(16 * nc, &back));
+    const int32_t *live = reinterpret_cast<const int32_t *>(back);
+    HIP_OK(hipMemcpyAsync(back, counts, 16 * nc, hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
     for (NetPlan *pl : net_plan) pl->scanned = true;
 
@@ -508,12 +520,14 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
         R.stage = reinterpret_cast<const int8_t *>(base + off[4 * i + 3]);
     }
     FoldBuild *dbuilds = reinterpret_cast<FoldBuild *>(ctx->fold_runs.as<char>() + al(B.hprops.size() * sizeof(FoldRun)));
-    HIP_OK(hipMemcpyAsync(dbuilds, builds.data(), builds.size() * sizeof(FoldBuild), hipMemcpyHostToDevice, s));
+    void *pb = nullptr;
+    IBMC_TRY(ctx->pin.take(builds.size() * sizeof(FoldBuild), &pb));
+    memcpy(pb, builds.data(), builds.size() * sizeof(FoldBuild));
+    HIP_OK(hipMemcpyAsync(dbuilds, pb, builds.size() * sizeof(FoldBuild), hipMemcpyHostToDevice, s));
     // enough workgroups per property to fill the device with a few properties
     const int parts = (int)std::max<int64_t>(1, std::min<int64_t>(32, 2 * ctx->n_cu / (int64_t)builds.size()));
     HIP_OK(launch_fold_gather(dnets, dbuilds, (int)builds.size(), parts, dprops, ctx->u0.as<int32_t>(), max_h1,
                               ctx->fold_runs.as<FoldRun>(), s));
-    HIP_OK(hipStreamSynchronize(s));   // the staging vectors go out of scope
     for (int v = 0; v < nv; ++v)
         if (!ids[v].empty()) {
             FoldBucket b;
@@ -640,26 +654,23 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
     //           float and lane kernels: kF32Queues counters, kQueueStride apart
     const int64_t q0 = 8, sc0 = 8 + NN, st0 = sc0 + B.n_slots, sp0 = st0 + B.n_slots;
     const int64_t fq0 = (sp0 + B.n_slots + kQueueStride - 1) / kQueueStride * kQueueStride;
-    int n_fold_inst = 0;
-    (void)fold_variants(&n_fold_inst);
-    // then one queue per instance of the folded enumeration, a line apart
-    const int64_t bq0 = fq0 + (int64_t)NN * kF32Queues * kQueueStride;
-    // and the folded jobs' counterexamples and ties
-    const int64_t fj0 = bq0 + (int64_t)n_fold_inst * kQueueStride;
     const int64_t cap = o->cex_capacity, tcap = o->near_tie_capacity;
     IBMC_TRY(ctx->ties.reserve((size_t)std::max<int64_t>(tcap, 1) * sizeof(DevRec)));
     int64_t max_h1 = 64;
     for (auto &pl : plans)
         max_h1 = std::max<int64_t>(max_h1, pl.net->act == IBMC_ACT_RELU_Q8 ? pl.net->qd.H[1] : pl.net->fd.HP[1]);
     IBMC_TRY(ctx->u0.reserve((size_t)n_props * max_h1 * 4));
-    std::vector<int32_t> u0_index(n_props), all_ids;
-    std::iota(u0_index.begin(), u0_index.end(), 0);
-    IBMC_TRY(ctx->u0_index.upload(u0_index.data(), u0_index.size() * 4, s));
+    std::vector<int32_t> all_ids;
 
     std::vector<FoldBucket> buckets;
     const std::vector<int> first_ids = plans.empty() ? std::vector<int>() : plans[0].ids;
     const ibmc_mlp *only_net = NN == 1 ? plans[0].net : nullptr;
     IBMC_TRY(fold_properties(ctx, props, o, B, level_sel, max_h1, resume != 0 || budget != 0, plans, buckets));
+
+    // then one queue per bucket, a line apart, and the folded jobs'
+    // counterexamples and ties
+    const int64_t bq0 = fq0 + (int64_t)NN * kF32Queues * kQueueStride;
+    const int64_t fj0 = bq0 + (int64_t)buckets.size() * kQueueStride;
 
     // plans: variants, jobs and chunk prefix sums of every network
     std::vector<EnumJob> jobs;
@@ -717,13 +728,15 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         }
         pl.n_jobs = jobs.size() - pl.job_off;
         if (pl.lane) {
-            const int g = lane_enum_grid(net->lane, ctx->n_cu);
+            int occ = 0;
+            const void *fn = lane_enum_kernel(net->lane);
+            if (fn) IBMC_TRY(resident_blocks(ctx, fn, 0, &occ));
+            const int g = ctx->n_cu * occ;
             if (g < 1) return fail(IBMC_E_UNIMPL, "no lane kernel for network %s", shape_key(net).c_str());
             pl.grid = (int)std::min<int64_t>(g, std::max<int64_t>(1, pl.total));
         } else if (q8) {
             int occ = 0;
-            HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, pl.v->fn, 256,
-                                                                (size_t)enum_lds_bytes(*pl.v, net->qd)));
+            IBMC_TRY(resident_blocks(ctx, pl.v->fn, (size_t)enum_lds_bytes(*pl.v, net->qd), &occ));
             if (occ < 1) return fail(IBMC_E_UNIMPL, "variant %s does not fit", pl.v->name);
             pl.grid = (int)std::min<int64_t>((int64_t)ctx->n_cu * occ, std::max<int64_t>(1, pl.total / 2));
             pl.batch = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, pl.total / ((int64_t)pl.grid * 32)));
@@ -741,7 +754,7 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         b.job_off = jobs.size();
         int occ = 0;
         const size_t lds = (size_t)fold_lds_bytes(*b.v, b.stage_max);
-        HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, b.v->fn, 256, lds));
+        IBMC_TRY(resident_blocks(ctx, b.v->fn, lds, &occ));
         if (occ < 1) return fail(IBMC_E_UNIMPL, "folded instance L%d width %d does not fit", b.v->L, b.v->kw);
         for (int pass = 0; pass < 2; ++pass) {
             // pass 0 counts the chunks, which sets the ticket size that the
@@ -796,8 +809,6 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         b.n_jobs = jobs.size() - b.job_off;
     }
     const int64_t n_ctr = fj0 + 2 * n_fold_jobs;
-    IBMC_TRY(ctx->counters.reserve(n_ctr * 8));
-    unsigned long long *ctr = ctx->counters.as<unsigned long long>();
     // record slots: the capacity plus one partly used block per wave of the
     // integer kernels (whose unused slots hold sentinels)
     int64_t rec_slots = cap;
@@ -805,17 +816,43 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
     for (auto &pl : plans)
         if (pl.net->act == IBMC_ACT_RELU_Q8 && !pl.lane) rec_slots += (int64_t)pl.grid * 4 * kRecBlock;
     IBMC_TRY(ctx->recs.reserve((size_t)std::max<int64_t>(rec_slots, 1) * sizeof(DevRec)));
-    IBMC_TRY(ctx->qcum.reserve(std::max<size_t>(qcum_all.size(), 1) * 8));
-    if (!qcum_all.empty())
-        HIP_OK(hipMemcpyAsync(ctx->qcum.p, qcum_all.data(), qcum_all.size() * 8, hipMemcpyHostToDevice, s));
-    for (size_t j = 0; j < jobs.size(); ++j)
-        jobs[j].qcum = (qcum_off[j] == (size_t)-1) ? nullptr : ctx->qcum.as<int64_t>() + qcum_off[j];
+    // the plan in one copy: [counters][jobs][prefix tables][property ids][u0 index]
     // (no jobs at all: every selected level is k = 0 or empty)
-    if (jobs.empty()) IBMC_TRY(ctx->jobs.reserve(sizeof(EnumJob)));
-    else IBMC_TRY(ctx->jobs.upload(jobs.data(), jobs.size() * sizeof(EnumJob), s));
-    if (all_ids.empty()) IBMC_TRY(ctx->prop_ids.reserve(4));
-    else IBMC_TRY(ctx->prop_ids.upload(all_ids.data(), all_ids.size() * 4, s));
-    HIP_OK(hipStreamSynchronize(s));  // host staging vectors may go now
+    auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    const size_t o_jobs = al(n_ctr * 8), o_qcum = o_jobs + al(std::max<size_t>(jobs.size(), 1) * sizeof(EnumJob));
+    const size_t o_ids = o_qcum + al(qcum_all.size() * 8), o_u0 = o_ids + al(std::max<size_t>(all_ids.size(), 1) * 4);
+    const size_t plan_bytes = o_u0 + (size_t)n_props * 4;
+    const bool behind = plan_bytes <= B.plan_room;
+    char *dplan = nullptr, *hplan = nullptr;
+    if (behind) {
+        dplan = ctx->props.as<char>() + B.o_plan;
+        hplan = B.host_in + B.o_plan;
+    } else {
+        IBMC_TRY(send_inputs(ctx, B));
+        IBMC_TRY(ctx->jobs.reserve(plan_bytes));
+        dplan = ctx->jobs.as<char>();
+        void *hp = nullptr;
+        IBMC_TRY(ctx->pin.take(plan_bytes, &hp));
+        hplan = reinterpret_cast<char *>(hp);
+    }
+    unsigned long long *const ctr = reinterpret_cast<unsigned long long *>(dplan);
+    const EnumJob *const d_jobs = reinterpret_cast<const EnumJob *>(dplan + o_jobs);
+    const int32_t *const d_ids = reinterpret_cast<const int32_t *>(dplan + o_ids);
+    const int32_t *const d_u0_index = reinterpret_cast<const int32_t *>(dplan + o_u0);
+    for (size_t j = 0; j < jobs.size(); ++j)
+        jobs[j].qcum = (qcum_off[j] == (size_t)-1) ? nullptr : reinterpret_cast<const int64_t *>(dplan + o_qcum) + qcum_off[j];
+    memset(hplan, 0, n_ctr * 8);
+    reinterpret_cast<unsigned long long *>(hplan)[2] = ~0ull;   // first_chunk, a minimum
+    if (!jobs.empty()) memcpy(hplan + o_jobs, jobs.data(), jobs.size() * sizeof(EnumJob));
+    if (!qcum_all.empty()) memcpy(hplan + o_qcum, qcum_all.data(), qcum_all.size() * 8);
+    if (!all_ids.empty()) memcpy(hplan + o_ids, all_ids.data(), all_ids.size() * 4);
+    std::iota(reinterpret_cast<int32_t *>(hplan + o_u0), reinterpret_cast<int32_t *>(hplan + o_u0) + n_props, 0);
+    if (behind && !B.in_sent) {
+        HIP_OK(hipMemcpyAsync(ctx->props.p, B.host_in, B.o_plan + plan_bytes, hipMemcpyHostToDevice, s));
+        B.in_sent = true;
+    } else {
+        HIP_OK(hipMemcpyAsync(dplan, hplan, plan_bytes, hipMemcpyHostToDevice, s));
+    }
 
     PropDev *dprops = ctx->props.as<PropDev>();
     // the table sigmoid's knots: sigma(-8 + i/16) rounded to FP32
@@ -837,7 +874,7 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
     // the clean pass of a network's properties, and its enumeration launch
     auto launch_clean = [&](const NetPlan &pl, size_t id_off, hipStream_t st) -> ibmc_status {
         const ibmc_mlp *net = pl.net;
-        const int32_t *ids = ctx->prop_ids.as<int32_t>() + id_off;
+        const int32_t *ids = d_ids + id_off;
         if (pl.scanned) return IBMC_OK;
         if (net->act == IBMC_ACT_RELU_Q8)
             HIP_OK(launch_clean_q8(net->qd, dprops, ids, (int32_t)pl.ids.size(), ctx->u0.as<int32_t>(), max_h1, st));
@@ -853,7 +890,7 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         if (pl.lane) {
             LaneParams P{};
             P.net = net->lane;
-            P.jobs = ctx->jobs.as<EnumJob>() + pl.job_off;
+            P.jobs = d_jobs + pl.job_off;
             P.n_jobs = (int32_t)pl.n_jobs;
             P.total_chunks = pl.total;
             P.slice = std::max<int64_t>(1, (pl.total + kF32Queues - 1) / kF32Queues);
@@ -879,7 +916,7 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         } else if (net->act == IBMC_ACT_RELU_Q8) {
             EnumParams P{};
             P.net = net->qd;
-            P.jobs = ctx->jobs.as<EnumJob>() + pl.job_off;
+            P.jobs = d_jobs + pl.job_off;
             P.n_jobs = (int32_t)pl.n_jobs;
             P.total_chunks = pl.limit;
             P.batch = pl.batch;
@@ -901,12 +938,12 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
             P.vb_lo = pl.vb_lo;
             P.vb_hi = pl.vb_hi;
             if (time_enum) HIP_OK(hipEventRecord(ctx->ek0, st));
-            HIP_OK(launch_enum_q8(*pl.v, pl.grid, P, ctx->u0.as<int32_t>(), max_h1, ctx->u0_index.as<int32_t>(), st));
+            HIP_OK(launch_enum_q8(*pl.v, pl.grid, P, ctx->u0.as<int32_t>(), max_h1, d_u0_index, st));
             if (time_enum) HIP_OK(hipEventRecord(ctx->ek1, st));
         } else {
             FEnumParams P{};
             P.net = net->fd;
-            P.jobs = ctx->jobs.as<EnumJob>() + pl.job_off;
+            P.jobs = d_jobs + pl.job_off;
             P.n_jobs = (int32_t)pl.n_jobs;
             P.total_chunks = pl.total;
             // slices of the chunk range, each with its own queue counter;
@@ -942,7 +979,7 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
     auto launch_bucket = [&](const FoldBucket &b, hipStream_t st) -> ibmc_status {
         const int bi = (int)(&b - buckets.data());
         FoldParams P{};
-        P.jobs = ctx->jobs.as<EnumJob>() + b.job_off;
+        P.jobs = d_jobs + b.job_off;
         P.n_jobs = (int32_t)b.n_jobs;
         P.batch = b.batch;
         P.total_chunks = b.total;
@@ -983,8 +1020,6 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         // Folded properties: which instances run depends on the images, so the
         // launches are not captured; the largest bucket runs on the
         // context's stream, the others beside it.
-        HIP_OK(launch_fill_u64(ctr, n_ctr, 0ull, s));
-        HIP_OK(launch_fill_u64(ctr + 2, 1, ~0ull, s));
         size_t id_off = 0;
         for (auto &pl : plans) {
             IBMC_TRY(launch_clean(pl, id_off, s));
@@ -1007,8 +1042,6 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         IBMC_TRY(bst);
         timed = true;
     } else if (NN <= 1) {
-        HIP_OK(launch_fill_u64(ctr, n_ctr, 0ull, s));
-        HIP_OK(launch_fill_u64(ctr + 2, 1, ~0ull, s));
         size_t id_off = 0;
         for (auto &pl : plans) {
             IBMC_TRY(launch_clean(pl, id_off, s));
@@ -1017,8 +1050,8 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
             timed = pl.n_jobs > 0 && pl.total > 0;
         }
     } else {
-        // one graph: counters cleared by a kernel (no memset node), then a
-        // branch per network on its own stream, joined back into s
+        // one graph: a branch per network on its own stream, joined back into
+        // s (the counters came cleared with the plan)
         IBMC_TRY(need_streams(NN));
         hipStream_t cs = ctx->side[0];  // capture origin: a private stream, never the caller's
         HIP_OK(hipStreamWaitEvent(cs, ctx->ek0, 0));
@@ -1044,8 +1077,8 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
             put(&pl.vb_hi, sizeof(pl.vb_hi));
             put(&nid, sizeof(nid));
         }
-        const void *bufs[] = {ctx->jobs.p, ctx->counters.p, ctx->recs.p, ctx->ties.p, ctx->u0.p, ctx->u0_index.p,
-                              ctx->prop_ids.p, ctx->props.p, ctx->qcum.p, ctx->flags_dev};
+        const void *bufs[] = {d_jobs, ctr, ctx->recs.p, ctx->ties.p, ctx->u0.p, d_u0_index,
+                              d_ids, ctx->props.p, dplan + o_qcum, ctx->flags_dev};
         put(bufs, sizeof(bufs));
         const int64_t scal[] = {n_ctr, rec_slots, tcap, max_h1, resume, sc0, st0, sp0, fq0, (int64_t)NN};
         put(scal, sizeof(scal));
@@ -1068,8 +1101,7 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         }
         HIP_OK(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
         ibmc_status cst = IBMC_OK;
-        hipError_t ce = launch_fill_u64(ctr, n_ctr, 0ull, cs);
-        if (ce == hipSuccess) ce = launch_fill_u64(ctr + 2, 1, ~0ull, cs);
+        hipError_t ce = hipSuccess;
         // every network's clean pass first, on the origin stream: in a branch
         // it would queue behind the other branches' persistent grids, which
         // hold every compute unit until they finish
@@ -1119,17 +1151,26 @@ graph_done:
         HIP_OK(hipEventRecord(ctx->ek1, s));
         timed = true;
     }
-    float ms = 0.f;
-    if (timed) {
-        HIP_OK(hipEventSynchronize(ctx->ek1));
-        HIP_OK(hipEventElapsedTime(&ms, ctx->ek0, ctx->ek1));
+    // gather: counters and clean labels in one wait
+    // (one copy where the counters lie close behind the properties)
+    const bool near = behind && B.o_plan <= ((size_t)128 << 10);
+    const size_t o_ctr = near ? B.o_plan : al(n_props * sizeof(PropDev));
+    void *back = nullptr;
+    IBMC_TRY(ctx->pin.take(o_ctr + n_ctr * 8, &back));
+    const unsigned long long *const h = reinterpret_cast<const unsigned long long *>((char *)back + o_ctr);
+    if (near) {
+        HIP_OK(hipMemcpyAsync(back, ctx->props.p, o_ctr + n_ctr * 8, hipMemcpyDeviceToHost, s));
+    } else {
+        HIP_OK(hipMemcpyAsync(back, ctx->props.p, n_props * sizeof(PropDev), hipMemcpyDeviceToHost, s));
+        HIP_OK(hipMemcpyAsync((char *)back + o_ctr, ctr, n_ctr * 8, hipMemcpyDeviceToHost, s));
     }
+    HIP_OK(hipEventRecord(ctx->ev1, s));
+    HIP_OK(hipStreamSynchronize(s));
+    memcpy(B.hprops.data(), back, n_props * sizeof(PropDev));
+    float ms = 0.f;
+    if (timed) HIP_OK(hipEventElapsedTime(&ms, ctx->ek0, ctx->ek1));
     kernel_seconds = ms * 1e-3;
     launches = timed ? NN + (int)buckets.size() : 0;
-    // gather
-    std::vector<unsigned long long> h(n_ctr);
-    HIP_OK(hipMemcpyAsync(h.data(), ctr, n_ctr * 8, hipMemcpyDeviceToHost, s));
-    HIP_OK(hipStreamSynchronize(s));
     tie_total = (int64_t)h[3];
     if (next_cursor) {
         // every queue ticket handed out was worked through: chunks below
@@ -1141,9 +1182,9 @@ graph_done:
             if (done < pl.total) *next_cursor = done;
         }
     }
-    slot_cex.assign(h.begin() + sc0, h.begin() + st0);
-    slot_ties.assign(h.begin() + st0, h.begin() + sp0);
-    slot_points.assign(h.begin() + sp0, h.begin() + sp0 + B.n_slots);
+    slot_cex.assign(h + sc0, h + st0);
+    slot_ties.assign(h + st0, h + sp0);
+    slot_points.assign(h + sp0, h + sp0 + B.n_slots);
     // An aborted check of one integer network returns a prefix of its
     // properties and levels, from whose end a resumed call continues: `cut`
     // is the first part that is not in it (by property, level, pixel).
@@ -1204,8 +1245,8 @@ graph_done:
                              direct_dev, recs, nout, slot_cex, slot_ties, rec_total, next_cursor));
     IBMC_TRY(fetch_sorted(ctx, ctx->ties.as<DevRec>(), nt, tcap, n_props - 1, max_k, max_rank, ties, direct_ties,
                           direct_dev, false, &nout, &nall));
-    HIP_OK(hipMemcpyAsync(B.hprops.data(), ctx->props.p, n_props * sizeof(PropDev), hipMemcpyDeviceToHost, s));
-    HIP_OK(hipStreamSynchronize(s));
+    // (ev1, recorded above, still ends the call's device work unless records were fetched)
+    B.ev1_ends = (nr == 0 || cap == 0) && (nt == 0 || tcap == 0);
     if (ctx->flags_host[0]) return fail(IBMC_E_ABORTED, "check aborted");
     return IBMC_OK;
 }
@@ -1216,11 +1257,9 @@ static bool rec_less(const CexRec &a, const CexRec &b) {
     return a.rank < b.rank;
 }
 
-ibmc_status check_batch_impl(ibmc_ctx *ctx, const ibmc_property *props_in, int32_t n_props, const ibmc_check_opts *o,
-                             ibmc_check_summary *outs, ibmc_cex *cex_buf, ibmc_cex *tie_buf, bool images_on_device,
-                             const int64_t *ball_r2) {
-    clear_error();
-    if (!ctx || !outs) return fail(IBMC_E_INVALID, "null ctx / outs");
+static ibmc_status check_batch_run(ibmc_ctx *ctx, const ibmc_property *props_in, int32_t n_props,
+                                   const ibmc_check_opts *o, ibmc_check_summary *outs, ibmc_cex *cex_buf,
+                                   ibmc_cex *tie_buf, bool images_on_device, const int64_t *ball_r2) {
     if (!props_in || n_props < 1) return fail(IBMC_E_INVALID, "no properties");
     // ball properties: m = 2 rd digits per pixel, no delta table
     std::vector<ibmc_property> pv(props_in, props_in + n_props);
@@ -1280,21 +1319,27 @@ ibmc_status check_batch_impl(ibmc_ctx *ctx, const ibmc_property *props_in, int32
     // images to the device
     std::vector<size_t> img_off(n_props, 0);
     size_t img_bytes = 0;
-    if (!images_on_device) {
+    if (!images_on_device)
         for (int i = 0; i < n_props; ++i) {
             img_off[i] = img_bytes;
             img_bytes += (size_t)round_up(props[i].net->dims[0], 16);
         }
-        IBMC_TRY(ctx->images.reserve(img_bytes));
-        std::vector<uint8_t> staging(img_bytes, 0);
-        for (int i = 0; i < n_props; ++i) memcpy(staging.data() + img_off[i], props[i].image, props[i].net->dims[0]);
-        HIP_OK(hipMemcpyAsync(ctx->images.p, staging.data(), img_bytes, hipMemcpyHostToDevice, s));
-        HIP_OK(hipStreamSynchronize(s));
-    }
+    // properties and images in one copy: [properties][images]
+    const size_t o_img = ((size_t)n_props * sizeof(PropDev) + 255) & ~(size_t)255;
+    B.in_bytes = o_img + img_bytes;
+    B.o_plan = (B.in_bytes + 255) & ~(size_t)255;
+    B.plan_room = thread_arena() ? 0 : (size_t)64 << 10;
+    IBMC_TRY(ctx->props.reserve(B.o_plan + B.plan_room));
+    void *hin = nullptr;
+    IBMC_TRY(ctx->pin.take(B.o_plan + B.plan_room, &hin));
+    B.host_in = reinterpret_cast<char *>(hin);
+    if (!images_on_device)
+        for (int i = 0; i < n_props; ++i)
+            memcpy((char *)hin + o_img + img_off[i], props[i].image, props[i].net->dims[0]);
     for (int i = 0; i < n_props; ++i) {
         PropDev &d = B.hprops[i];
         memset(&d, 0, sizeof(d));
-        d.image = images_on_device ? props[i].image : ctx->images.as<uint8_t>() + img_off[i];
+        d.image = images_on_device ? props[i].image : ctx->props.as<uint8_t>() + o_img + img_off[i];
         d.m = props[i].n_deltas;
         d.n = props[i].net->dims[0];
         if (ball_r2 && ball_r2[i] >= 0) {
@@ -1308,7 +1353,7 @@ ibmc_status check_batch_impl(ibmc_ctx *ctx, const ibmc_property *props_in, int32
         for (int k = props[i].k_min; k <= props[i].k_max; k += props[i].k_step) B.level_k[i].push_back(k);
         B.n_slots += (int)B.level_k[i].size();
     }
-    IBMC_TRY(ctx->props.upload(B.hprops.data(), B.hprops.size() * sizeof(PropDev), s));
+    memcpy(hin, B.hprops.data(), B.hprops.size() * sizeof(PropDev));
 
     std::vector<std::vector<int>> done_levels(n_props);
     std::vector<unsigned long long> cex_acc(B.n_slots, 0), ties_acc(B.n_slots, 0), pts_acc(B.n_slots, 0);
@@ -1368,8 +1413,10 @@ ibmc_status check_batch_impl(ibmc_ctx *ctx, const ibmc_property *props_in, int32
             }
         if (st == IBMC_E_ABORTED) break;
     }
-    HIP_OK(hipEventRecord(ctx->ev1, s));
-    HIP_OK(hipEventSynchronize(ctx->ev1));
+    if (!B.ev1_ends) {
+        HIP_OK(hipEventRecord(ctx->ev1, s));
+        HIP_OK(hipEventSynchronize(ctx->ev1));
+    }
     float ms = 0.f;
     HIP_OK(hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1));
     ctx->last_kernel_seconds = ksec;
@@ -1423,6 +1470,18 @@ ibmc_status check_batch_impl(ibmc_ctx *ctx, const ibmc_property *props_in, int32
     if (rec_total > o->cex_capacity || tie_total > o->near_tie_capacity) return IBMC_W_TRUNCATED;
     if (next_cursor >= 0) return IBMC_W_PARTIAL;
     return IBMC_OK;
+}
+
+ibmc_status check_batch_impl(ibmc_ctx *ctx, const ibmc_property *props, int32_t n_props, const ibmc_check_opts *o,
+                             ibmc_check_summary *outs, ibmc_cex *cex_buf, ibmc_cex *tie_buf, bool images_on_device,
+                             const int64_t *ball_r2) {
+    clear_error();
+    if (!ctx || !outs) return fail(IBMC_E_INVALID, "null ctx / outs");
+    IBMC_TRY(ctx->pin.reset());
+    const ibmc_status st = check_batch_run(ctx, props, n_props, o, outs, cex_buf, tie_buf, images_on_device, ball_r2);
+    // an early return may leave copies from the pinned pieces in flight
+    if (st < 0 && st != IBMC_E_ABORTED) (void)hipStreamSynchronize(ctx->stream);
+    return st;
 }
 
 }  // namespace ibmc

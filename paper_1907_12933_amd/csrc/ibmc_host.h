@@ -74,6 +74,20 @@ struct DevBuf {
     template <class T> T *as() const { return reinterpret_cast<T *>(p); }
 };
 
+// Pinned host memory of one call's uploads and read-backs: pieces are taken in
+// order and stay valid until the next call's reset (a call returns with its
+// stream idle).  Copies from and to it queue without a wait on the host.
+struct PinPool {
+    std::vector<std::pair<char *, size_t>> blocks;   // the last one is being carved
+    size_t used = 0;
+    PinPool() = default;
+    PinPool(const PinPool &) = delete;
+    PinPool &operator=(const PinPool &) = delete;
+    ~PinPool();
+    ibmc_status take(size_t n, void **out);          // 256-byte aligned
+    ibmc_status reset();                             // several blocks become one of their total size
+};
+
 }  // namespace ibmc
 
 struct ibmc_ctx {
@@ -86,8 +100,10 @@ struct ibmc_ctx {
     int32_t *flags_host = nullptr;   // [0] abort request, [1] first hit
     int32_t *flags_dev = nullptr;    // device view of flags_host
     // scratch of the check driver (grow-only)
-    ibmc::DevBuf images, props, jobs, qcum, u0, u0_index, prop_ids, counters, recs, ties, order;
+    ibmc::DevBuf images, props, jobs, u0, prop_ids, counters, recs, ties, order;
     ibmc::DevBuf u0f, sortbuf;
+    ibmc::PinPool pin;
+    std::map<std::pair<const void *, size_t>, int> occupancy;   // resident workgroups by kernel and LDS bytes
     ibmc::DevBuf lut;                  // the table sigmoid's knots (built on first use)
     ibmc::DevBuf fold_in, fold_ws, fold_runs, fold_data;   // folded properties: see run_levels
     ibmc::DevBuf recout;  // sorted records in the public layout, on their way to a host buffer
@@ -142,6 +158,9 @@ struct ibmc_mlp {
 
 namespace ibmc {
 std::string shape_key(const ibmc_mlp *m);
+// Resident 256-thread workgroups per compute unit of a kernel at `lds` bytes of
+// dynamic LDS, asked once per context.
+ibmc_status resident_blocks(ibmc_ctx *ctx, const void *fn, size_t lds, int *occ);
 PropParams prop_views(const ibmc_proposer *p);
 const EnumVariant *pick_variant(ibmc_ctx *ctx, const ibmc_mlp *net);
 bool use_lane(ibmc_ctx *ctx, const ibmc_mlp *net, bool allowed);

@@ -91,6 +91,53 @@ ibmc_status DevBuf::upload(const void *src, size_t n, hipStream_t s) {
     return IBMC_OK;
 }
 
+PinPool::~PinPool() {
+    for (auto &b : blocks) (void)hipHostFree(b.first);
+}
+
+ibmc_status PinPool::take(size_t n, void **out) {
+    const size_t need = (std::max<size_t>(n, 1) + 255) & ~(size_t)255;
+    if (blocks.empty() || blocks.back().second - used < need) {
+        const size_t size = std::max<size_t>(need, (size_t)256 << 10);
+        void *p = nullptr;
+        if (hipHostMalloc(&p, size, hipHostMallocDefault) != hipSuccess)
+            return fail(IBMC_E_OOM, "hipHostMalloc(%zu) failed", size);
+        blocks.emplace_back((char *)p, size);
+        used = 0;
+    }
+    *out = blocks.back().first + used;
+    used += need;
+    return IBMC_OK;
+}
+
+ibmc_status PinPool::reset() {
+    if (blocks.size() > 1) {
+        size_t total = 0;
+        for (auto &b : blocks) {
+            total += b.second;
+            HIP_OK(hipHostFree(b.first));
+        }
+        blocks.clear();
+        void *p = nullptr;
+        if (hipHostMalloc(&p, total, hipHostMallocDefault) == hipSuccess) blocks.emplace_back((char *)p, total);
+        else (void)hipGetLastError();   // taken piece by piece again
+    }
+    used = 0;
+    return IBMC_OK;
+}
+
+ibmc_status resident_blocks(ibmc_ctx *ctx, const void *fn, size_t lds, int *occ) {
+    const auto key = std::make_pair(fn, lds);
+    const auto it = ctx->occupancy.find(key);
+    if (it != ctx->occupancy.end()) {
+        *occ = it->second;
+        return IBMC_OK;
+    }
+    HIP_OK(hipOccupancyMaxActiveBlocksPerMultiprocessor(occ, fn, 256, lds));
+    ctx->occupancy[key] = *occ;
+    return IBMC_OK;
+}
+
 }  // namespace ibmc
 
 using namespace ibmc;

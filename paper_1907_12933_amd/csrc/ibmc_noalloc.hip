@@ -76,6 +76,7 @@ static ibmc_status scratch_need(ibmc_ctx *ctx, const ibmc_mlp *net, int32_t n_de
     b += al256(sort_scratch_bytes(rec_slots)) + al256(sort_scratch_bytes(tcap));
     if (!o->records_on_device)
         b += al256((size_t)std::max<int64_t>(cap, 1) * sizeof(CexRec)) + al256((size_t)std::max<int64_t>(tcap, 1) * sizeof(CexRec));
+    b += 2 * 512;                                                    // record counts of short lists
     *need = b;
     return IBMC_OK;
 }
@@ -109,8 +110,7 @@ extern "C" ibmc_status ibmc_check_property_noalloc(ibmc_ctx *ctx, const ibmc_mlp
     p.k_max = opts->k_max;
     p.k_step = opts->k_step;
     // the context's own buffers step aside; empty ones carve the arena
-    DevBuf *mine[] = {&ctx->images, &ctx->props, &ctx->jobs, &ctx->qcum, &ctx->u0, &ctx->u0_index,
-                      &ctx->prop_ids, &ctx->counters, &ctx->recs, &ctx->ties, &ctx->order, &ctx->u0f,
+    DevBuf *mine[] = {&ctx->images, &ctx->props, &ctx->jobs, &ctx->u0, &ctx->prop_ids, &ctx->counters, &ctx->recs, &ctx->ties, &ctx->order, &ctx->u0f,
                       &ctx->sortbuf, &ctx->recout};
     constexpr int NB = sizeof(mine) / sizeof(mine[0]);
     DevBuf saved[NB];

@@ -37,6 +37,8 @@ struct LaneParams {
 bool lane_eligible(const int *dims, int L);
 // Instance widths of a hidden layer of h units.
 int lane_width(int h);
+// The instance for the network (null: none).
+const void *lane_enum_kernel(const LaneNetDev &net);
 // Persistent grid of the instance for the network (0: no instance).
 int lane_enum_grid(const LaneNetDev &net, int n_cu);
 hipError_t launch_enum_lane(int grid, const LaneParams &P, hipStream_t s);
