@@ -174,8 +174,10 @@ __global__ void __launch_bounds__(256, KW <= 64 ? 3 : 2) enum_fold_kernel(FoldPa
     int lo2 = -64, hi2 = 63;
     asm("" : "+v"(lo2));
     asm("" : "+v"(hi2));
-    // records: slots come in blocks of kRecBlock from one atomic
+    // records: slots come in blocks from one atomic, 8 at first (a wave with a
+    // few records leaves few unused), then twice as many, up to kRecBlock
     int64_t rnext = 0, rend = 0;
+    int rblock = 8;
 
     while (true) {
         if (threadIdx.x == 0) {
@@ -473,9 +475,12 @@ __global__ void __launch_bounds__(256, KW <= 64 ? 3 : 2) enum_fold_kernel(FoldPa
                 ncex += n;
                 const int64_t room = rend - rnext;
                 int64_t nb = 0;
+                int got = 0;
                 if (n > room) {
+                    got = max(rblock, (int)(n - room));
+                    rblock = min(2 * rblock, kRecBlock);
                     unsigned long long s = 0;
-                    if (lane == 0) s = atomicAdd(P.rec_count, (unsigned long long)kRecBlock);
+                    if (lane == 0) s = atomicAdd(P.rec_count, (unsigned long long)got);
                     nb = (int64_t)wave_uniform(s);
                 }
                 int pl = plast[0], il = ilast[0];
@@ -497,7 +502,7 @@ __global__ void __launch_bounds__(256, KW <= 64 ? 3 : 2) enum_fold_kernel(FoldPa
                 }
                 if (n > room) {
                     rnext = nb + (n - room);
-                    rend = nb + kRecBlock;
+                    rend = nb + got;
                 } else {
                     rnext += n;
                 }

@@ -205,6 +205,27 @@ static ibmc_status fetch_sorted(ibmc_ctx *ctx, const DevRec *drecs, int64_t n, i
     outv.clear();
     *nout = *nall = 0;
     if (n == 0 || keep == 0) return IBMC_OK;
+    if (n <= kSortSmall && sort_key_bits(max_prop, max_k, max_rank) <= 64) {
+        // one workgroup sorts and unpacks; the records and their number come
+        // back in one copy
+        const int64_t m = std::min(n, keep);
+        const size_t o_rec = 256;
+        IBMC_TRY(ctx->recout.reserve(o_rec + (direct_dev ? 0 : (size_t)m * sizeof(CexRec))));
+        char *buf = ctx->recout.as<char>();
+        CexRec *dout = direct_dev ? direct : reinterpret_cast<CexRec *>(buf + o_rec);
+        HIP_OK(launch_sort_small(drecs, n, m, max_prop, max_k, max_rank, dout, reinterpret_cast<int64_t *>(buf), s));
+        const size_t bytes = o_rec + (direct_dev ? 0 : (size_t)m * sizeof(CexRec));
+        void *hp = nullptr;
+        IBMC_TRY(ctx->pin.take(bytes, &hp));
+        HIP_OK(hipMemcpyAsync(hp, buf, bytes, hipMemcpyDeviceToHost, s));
+        HIP_OK(hipStreamSynchronize(s));
+        const int64_t valid = *reinterpret_cast<const int64_t *>(hp);
+        *nout = *nall = valid;
+        const CexRec *r = reinterpret_cast<const CexRec *>((char *)hp + o_rec);
+        if (direct && !direct_dev) memcpy(direct, r, valid * sizeof(CexRec));
+        else if (!direct) outv.assign(r, r + valid);
+        return IBMC_OK;
+    }
     IBMC_TRY(ctx->sortbuf.reserve(sort_scratch_bytes(n)));
     SortScratch S;
     sort_scratch_carve(ctx->sortbuf.p, n, S);

@@ -33,4 +33,14 @@ ibmc_status_t sort_records_device(const DevRec *recs, int64_t n, int max_prop, i
 // write them in the public layout (ibmc_cex) to out (device memory).
 hipError_t sorted_to_records(const SortScratch &S, int64_t m, CexRec *out, hipStream_t s);
 
+// Key bits that records of these bounds need.
+int sort_key_bits(int max_prop, int max_k, int64_t max_rank);
+
+// Up to kSortSmall record slots in one launch of one workgroup: sorted by
+// (prop, k, rank), sentinels dropped, the first m unpacked into out; *count
+// receives how many those are.  Needs sort_key_bits <= 64.
+constexpr int64_t kSortSmall = 4096;
+hipError_t launch_sort_small(const DevRec *recs, int64_t n, int64_t m, int max_prop, int max_k, int64_t max_rank,
+                             CexRec *out, int64_t *count, hipStream_t s);
+
 }  // namespace ibmc

@@ -59,6 +59,83 @@ static int key_bits(int max_prop, int max_k, int64_t max_rank, int *kshift, int 
     return rbits + kb + pb;
 }
 
+int sort_key_bits(int max_prop, int max_k, int64_t max_rank) {
+    int ks = 0, ps = 0;
+    return key_bits(max_prop, max_k, max_rank, &ks, &ps);
+}
+
+// Bitonic sort of N >= n keys (a power of two, filled up with sentinels) and
+// their payload in the LDS of one workgroup.  A short list is bound by launches:
+// the radix sort takes 30 us on the device in eleven launches and clears and
+// 50 to 100 us from the first to the last; this one launch takes 6 us for 64
+// slots, 15 for 512, 33 for 2,048 and 56 for 4,096, and would take 100 for
+// 8,192, where the line is (kSortSmall).
+__global__ void __launch_bounds__(1024) sort_small_kernel(const DevRec *recs, int n, int N, int m, int kshift, int pshift,
+                                                          CexRec *out, int64_t *count) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    uint64_t *key = reinterpret_cast<uint64_t *>(lds);
+    uint32_t *val = reinterpret_cast<uint32_t *>(key + N);
+    __shared__ int valid;
+    if (threadIdx.x == 0) valid = 0;
+    __syncthreads();
+    int mine = 0;
+    for (int i = threadIdx.x; i < N; i += blockDim.x) {
+        uint64_t k = ~0ull;
+        uint32_t v = 0;
+        if (i < n) {
+            const DevRec r = recs[i];
+            if (r.prop >= 0) {
+                k = ((uint64_t)r.prop << pshift) | ((uint64_t)((uint32_t)r.klab >> 24) << kshift) | (uint64_t)r.rank;
+                v = (uint32_t)r.klab & 0xffffffu;
+                ++mine;
+            }
+        }
+        key[i] = k;
+        val[i] = v;
+    }
+    if (mine) atomicAdd(&valid, mine);
+    __syncthreads();
+    for (int size = 2; size <= N; size <<= 1)
+        for (int d = size >> 1; d > 0; d >>= 1) {
+            for (int t = threadIdx.x; t < N / 2; t += blockDim.x) {
+                const int i = 2 * t - (t & (d - 1)), j = i + d;
+                const uint64_t a = key[i], b = key[j];
+                if ((a > b) == ((i & size) == 0)) {
+                    key[i] = b;
+                    key[j] = a;
+                    const uint32_t x = val[i];
+                    val[i] = val[j];
+                    val[j] = x;
+                }
+            }
+            __syncthreads();
+        }
+    const int nv = min(valid, m);
+    const uint64_t rmask = (1ull << kshift) - 1ull, kmask = (1ull << (pshift - kshift)) - 1ull;
+    for (int i = threadIdx.x; i < nv; i += blockDim.x) {
+        const uint64_t k = key[i];
+        CexRec r;
+        r.prop = (int32_t)(pshift >= 64 ? 0 : (k >> pshift));
+        r.k = (int32_t)((k >> kshift) & kmask);
+        r.rank = (int64_t)(k & rmask);
+        r.label = (int32_t)val[i];
+        r.reserved = 0;
+        out[i] = r;
+    }
+    if (threadIdx.x == 0) *count = nv;
+}
+
+hipError_t launch_sort_small(const DevRec *recs, int64_t n, int64_t m, int max_prop, int max_k, int64_t max_rank,
+                             CexRec *out, int64_t *count, hipStream_t s) {
+    int kshift = 0, pshift = 0;
+    if (n < 1 || n > kSortSmall || key_bits(max_prop, max_k, max_rank, &kshift, &pshift) > 64) return hipErrorInvalidValue;
+    int N = 64;
+    while (N < n) N *= 2;
+    hipLaunchKernelGGL(sort_small_kernel, dim3(1), dim3(std::min(1024, std::max(64, N / 2))), (size_t)N * 12, s, recs,
+                       (int)n, N, (int)m, kshift, pshift, out, count);
+    return hipGetLastError();
+}
+
 static size_t radix_tmp_bytes(int64_t n) {
     size_t bytes = 0;
     rocprim::double_buffer<uint64_t> kb(nullptr, nullptr);
