@@ -18,6 +18,8 @@
 
 namespace ibmc {
 
+typedef float v4f __attribute__((ext_vector_type(4)));
+
 // Load through the constant address space: a wave-uniform address becomes
 // one scalar-cache load for the whole wave (weights, biases and the clean
 // potentials are read-only while the kernels run).
@@ -79,19 +81,20 @@ __device__ __forceinline__ float eff_delta(int xv, int d) {
     return (float)(clamp_pixel(xv + d) - xv) * (1.0f / 256.0f);
 }
 
-// Lowest-index largest logit of the first nc, its value and the margin to the
-// runner-up (infinite with one class).
+// Lowest-index largest logit, its value and the margin to the runner-up
+// (infinite with one class).  Classes past the network's hold -infinity.
 template <int NCP>
-__device__ __forceinline__ void decide_f32(const float (&z)[NCP], int nc, int &best, float &top, float &margin) {
+__device__ __forceinline__ void decide_f32(const float (&z)[NCP], int &best, float &top, float &margin) {
     best = 0;
     top = z[0];
-#pragma unroll
-    for (int j = 1; j < NCP; ++j)
-        if (j < nc && z[j] > top) { top = z[j]; best = j; }
     float second = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < NCP; ++j)
-        if (j < nc && j != best) second = fmaxf(second, z[j]);
+    for (int j = 1; j < NCP; ++j) {
+        const bool gt = z[j] > top;
+        second = gt ? top : (z[j] > second ? z[j] : second);
+        top = gt ? z[j] : top;
+        best = gt ? j : best;
+    }
     margin = top - second;
 }
 
@@ -210,86 +213,113 @@ __device__ __forceinline__ void decode_point_dev(int n, int m, int k, int64_t ra
 
 constexpr int kLaneWaves = 4;  // waves per workgroup of the lane kernels
 
-// Layers >= 2 of the lane's point from its first-layer activations a1.
-// a2w: this wave's LDS columns ([H2][64] of the second hidden layer, or
-// [NCP][64] of the logits with one hidden layer); each lane touches only its
-// own column.
-template <int H1, int H2, int NCP>
-__device__ __forceinline__ void lane_upper(const FNetDev &net, const float (&a1)[H1], float *a2w, int lane,
-                                           float (&z)[NCP], bool use_tab, const float *tab) {
-    if constexpr (H2 == 0) {
-        const float *W = opaque(net.WP[2]);
-        const float *B = opaque(net.bP[2]);
-        // eight classes per step (eight scalar weights per input in flight),
-        // each step's logits parked in this lane's LDS column
-#pragma unroll 1
-        for (int j0 = 0; j0 < NCP; j0 += 8) {
-            float tot[8];
+// One layer of the lanes' points on the matrix cores: the 4x4x1 FP32 product
+// of sixteen blocks gives every lane, from its own activation (B: point
+// 4b + j of block b in lane 4b + j), four outputs of its own point (D: one
+// output per register), and the broadcast of one block's A lets one register
+// hold the weights of sixteen inputs: lane 4b + i has input 16 kb + b, output
+// 4 q + i.  Each product is one fma per output (also for subnormal values),
+// so the order of operations is the one stated above.  The scalar form, four
+// fma with weights from the scalar cache, took twice the matrix pipe's time
+// and all of it on the vector unit, which the sigmoids need: 196-128-64-10
+// 2.5 -> 4.5, 100-64-10 14 -> 21, 35-32-16-5 24 -> 32, 35-16-5 67 -> 77
+// billion points per second; the vector unit bounds it still (sigmoids, and
+// for the small networks the decision and the chunk's set-up).
+// w[kb * QS + q]: QS quads of outputs; the first Q are computed.
+template <int K, int QS>
+__device__ __forceinline__ void lane_weights(const float *W, int ld, int lane, float (&w)[K / 16 * QS]) {
+    const unsigned at = (unsigned)((lane >> 2) * ld + (lane & 3));
 #pragma unroll
-            for (int j = 0; j < 8; ++j) tot[j] = cld(B + j0 + j);
+    for (int kb = 0; kb < K / 16; ++kb)
 #pragma unroll
-            for (int ib = 0; ib < H1; ib += kF32SumBlock) {
-                float part[8];
+        for (int q = 0; q < QS; ++q) w[kb * QS + q] = gld(W + (16 * kb * ld + 4 * q) + at);
+}
+
+template <int K, int Q, int QS>
+__device__ __forceinline__ void lane_rows(const float (&w)[K / 16 * QS], const float (&a)[K], v4f (&tot)[Q]) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) part[j] = 0.0f;
+    for (int ib = 0; ib < K; ib += kF32SumBlock) {
+        v4f part[Q];
 #pragma unroll
-                for (int i = ib; i < ib + kF32SumBlock && i < H1; ++i)
+        for (int q = 0; q < Q; ++q) part[q] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) part[j] = fmaf(cld(W + i * NCP + j0 + j), a1[i], part[j]);
-#pragma unroll
-                for (int j = 0; j < 8; ++j) tot[j] += part[j];
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) a2w[(j0 + j) * 64 + lane] = tot[j];
+        for (int kb = ib / 16; kb < (ib + kF32SumBlock) / 16 && kb < K / 16; ++kb) {
+#define IBMC_ROW(k)                                                                                           \
+    _Pragma("unroll") for (int q = 0; q < Q; ++q) part[q] =                                                   \
+        __builtin_amdgcn_mfma_f32_4x4x1f32(w[kb * QS + q], a[16 * kb + k], part[q], 4, k, 0)
+            IBMC_ROW(0);  IBMC_ROW(1);  IBMC_ROW(2);  IBMC_ROW(3);  IBMC_ROW(4);  IBMC_ROW(5);  IBMC_ROW(6);  IBMC_ROW(7);
+            IBMC_ROW(8);  IBMC_ROW(9);  IBMC_ROW(10); IBMC_ROW(11); IBMC_ROW(12); IBMC_ROW(13); IBMC_ROW(14); IBMC_ROW(15);
+#undef IBMC_ROW
         }
 #pragma unroll
-        for (int j = 0; j < NCP; ++j) z[j] = a2w[j * 64 + lane];
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) tot[q][i] += part[q][i];
+    }
+}
+
+// The last layer's weights stay in registers (NCP / 4 per sixteen inputs).
+template <int H1, int H2, int NCP>
+struct LaneOut {
+    static constexpr int K = H2 > 0 ? H2 : H1, QS = NCP / 4;
+    float w[K / 16 * QS];
+    __device__ __forceinline__ void load(const FNetDev &net, int lane) {
+        lane_weights<K, QS>(net.WP[H2 > 0 ? 3 : 2], NCP, lane, w);
+    }
+};
+
+// Layers >= 2 of the lane's point from its first-layer activations a1; z of
+// the first 4 Q classes, -infinity past the network's.  a2w: this wave's LDS
+// columns [H2][64] of the second hidden layer; each lane touches only its own.
+template <int H1, int H2, int NCP, int Q>
+__device__ __forceinline__ void lane_upper(const FNetDev &net, const LaneOut<H1, H2, NCP> &out,
+                                           const float (&a1)[H1], float *a2w, int lane, float (&z)[NCP], bool use_tab,
+                                           const float *tab) {
+    constexpr int QS = NCP / 4;
+    const float *B = opaque(net.bP[H2 > 0 ? 3 : 2]);
+    v4f tot[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tot[q][i] = cld(B + 4 * q + i);
+    if constexpr (H2 == 0) {
+        lane_rows<H1, Q, QS>(out.w, a1, tot);
     } else {
         const float *W2 = opaque(net.WP[2]);
         const float *B2 = opaque(net.bP[2]);
-        // second hidden layer, eight units per step, into this lane's LDS column
+        // second hidden layer, sixteen units per step, into this lane's LDS column
 #pragma unroll 1
-        for (int jb = 0; jb < H2; jb += 8) {
-            float tot[8];
+        for (int jb = 0; jb < H2; jb += 16) {
+            float w2[H1 / 16 * 4];
+            lane_weights<H1, 4>(W2 + jb, H2, lane, w2);
+            v4f t2[4];
 #pragma unroll
-            for (int jj = 0; jj < 8; ++jj) tot[jj] = cld(B2 + jb + jj);
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int ib = 0; ib < H1; ib += kF32SumBlock) {
-                float part[8];
+                for (int i = 0; i < 4; ++i) t2[q][i] = cld(B2 + jb + 4 * q + i);
+            lane_rows<H1, 4, 4>(w2, a1, t2);
 #pragma unroll
-                for (int jj = 0; jj < 8; ++jj) part[jj] = 0.0f;
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int i = ib; i < ib + kF32SumBlock && i < H1; ++i)
-#pragma unroll
-                    for (int jj = 0; jj < 8; ++jj) part[jj] = fmaf(cld(W2 + i * H2 + jb + jj), a1[i], part[jj]);
-#pragma unroll
-                for (int jj = 0; jj < 8; ++jj) tot[jj] += part[jj];
-            }
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj) a2w[(jb + jj) * 64 + lane] = act_f32(tot[jj], use_tab, tab);
+                for (int i = 0; i < 4; ++i) a2w[(jb + 4 * q + i) * 64 + lane] = act_f32(t2[q][i], use_tab, tab);
         }
-        const float *W3 = opaque(net.WP[3]);
-        const float *B3 = opaque(net.bP[3]);
+        float a2[H2];
 #pragma unroll
-        for (int j0 = 0; j0 < NCP; j0 += 8) {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) z[j0 + j] = cld(B3 + j0 + j);
-#pragma unroll
-            for (int ib = 0; ib < H2; ib += kF32SumBlock) {
-                float part[8];
-#pragma unroll
-                for (int j = 0; j < 8; ++j) part[j] = 0.0f;
-#pragma unroll 4
-                for (int i = ib; i < ib + (H2 < kF32SumBlock ? H2 : kF32SumBlock); ++i) {
-                    const float a = a2w[i * 64 + lane];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) part[j] = fmaf(cld(W3 + i * NCP + j0 + j), a, part[j]);
-                }
-#pragma unroll
-                for (int j = 0; j < 8; ++j) z[j0 + j] += part[j];
-            }
-        }
+        for (int j = 0; j < H2; ++j) a2[j] = a2w[j * 64 + lane];
+        lane_rows<H2, Q, QS>(out.w, a2, tot);
     }
+#pragma unroll
+    for (int j = 0; j < NCP; ++j) z[j] = j < 4 * Q ? tot[j / 4 < Q ? j / 4 : 0][j & 3] : -INFINITY;
+}
+
+// The same with the quads that nc classes need, and the decision.
+template <int H1, int H2, int NCP>
+__device__ __forceinline__ void lane_decide(const FNetDev &net, const LaneOut<H1, H2, NCP> &out, int nc,
+                                            const float (&a1)[H1], float *a2w, int lane, float (&z)[NCP], bool use_tab,
+                                            const float *tab, int &best, float &top, float &margin) {
+    if (NCP == 16 && nc <= 12) lane_upper<H1, H2, NCP, NCP == 16 ? 3 : 2>(net, out, a1, a2w, lane, z, use_tab, tab);
+    else lane_upper<H1, H2, NCP, NCP / 4>(net, out, a1, a2w, lane, z, use_tab, tab);
+    decide_f32<NCP>(z, best, top, margin);
 }
 
 // First-layer potentials before the last pixel: v_j = u0_j, then one fma
@@ -332,10 +362,12 @@ __device__ __forceinline__ void segment_prefix(const Cursor &c, int (&pp)[kMaxK]
 // fixed) the wave computes v_j before the last pixel once into its LDS slot;
 // per property it keeps the clean label in a register; a chunk then loads
 // only its own pixels, deltas and first-layer rows.
+// (The waves per SIMD keep the registers that the compiler would spend on
+// addresses in check: 128-64 took 416 and ran one wave.)
 template <int H1, int H2, int NCP, bool TAB>
-__global__ void __launch_bounds__(256) enum_f32_lane_kernel(FEnumParams P) {
+__global__ void __launch_bounds__(256, H1 <= 16 ? 4 : H1 <= 32 ? 3 : 2) enum_f32_lane_kernel(FEnumParams P) {
     constexpr int CH = kF32LaneChunk;
-    __shared__ float a2s[kLaneWaves][H2 > 0 ? H2 : NCP][64];
+    __shared__ float a2s[kLaneWaves][H2 > 0 ? H2 : 1][64];
     __shared__ __attribute__((aligned(16))) float bases[kLaneWaves][H1];
     __shared__ float tab[kLutIntervals + 1];
     // TAB is a compile-time switch: a run-time choice inside the unrolled
@@ -345,6 +377,8 @@ __global__ void __launch_bounds__(256) enum_f32_lane_kernel(FEnumParams P) {
     float *a2w = &a2s[threadIdx.x >> 6][0][0];
     float *base = &bases[threadIdx.x >> 6][0];
     const int nc = P.net.dims[P.net.L];
+    LaneOut<H1, H2, NCP> out;
+    out.load(P.net, lane);
     Cursor c;
     int64_t cur = 0, end = 0;
     bool seg_new = true;
@@ -392,13 +426,15 @@ __global__ void __launch_bounds__(256) enum_f32_lane_kernel(FEnumParams P) {
             a1[4 * j4 + 3] = act_f32(fmaf(e, wrow[j4].w, b.w), use_tab, tab);
         }
         float z[NCP];
-        lane_upper<H1, H2, NCP>(P.net, a1, a2w, lane, z, use_tab, tab);
         int best;
         float top, margin;
-        decide_f32<NCP>(z, nc, best, top, margin);
+        lane_decide<H1, H2, NCP>(P.net, out, nc, a1, a2w, lane, z, use_tab, tab, best, top, margin);
         bool near = valid && margin <= P.tie_rel * fmaxf(1.0f, fabsf(top));
         bool viol = valid && best != label0;
         if (P.literal) {
+            // (opaque: the compiler would compute this for every point and select)
+#pragma unroll
+            for (int j = 0; j < NCP; ++j) asm volatile("" : "+v"(z[j]));
             // the threshold literal: the desired (clean) class below V, another above
             float zd = z[0], other = -INFINITY;
 #pragma unroll
@@ -420,7 +456,7 @@ __global__ void __launch_bounds__(256) enum_f32_lane_kernel(FEnumParams P) {
 // in the same sequence of operations.
 template <int H1, int H2, int NCP, bool TAB>
 __global__ void __launch_bounds__(256) eval_f32_lane_kernel(F32EvalParams E) {
-    __shared__ float a2s[kLaneWaves][H2 > 0 ? H2 : NCP][64];
+    __shared__ float a2s[kLaneWaves][H2 > 0 ? H2 : 1][64];
     __shared__ float tab[kLutIntervals + 1];
     const bool use_tab = TAB && stage_table(E.lut, tab);
     const int lane = __lane_id();
@@ -453,11 +489,12 @@ __global__ void __launch_bounds__(256) eval_f32_lane_kernel(F32EvalParams E) {
     for (int j = 0; j < H1; ++j)
         a1[j] = act_f32(fmaf(e, w1[j], prefix_potential<H1>(E.net, u0, np, pp, ee, j)), use_tab, tab);
     float z[NCP];
-    lane_upper<H1, H2, NCP>(E.net, a1, a2w, lane, z, use_tab, tab);
     const int nc = E.net.dims[E.net.L];
+    LaneOut<H1, H2, NCP> out;
+    out.load(E.net, lane);
     int best;
     float top, margin;
-    decide_f32<NCP>(z, nc, best, top, margin);
+    lane_decide<H1, H2, NCP>(E.net, out, nc, a1, a2w, lane, z, use_tab, tab, best, top, margin);
     if (!ok) return;
     if (E.label_props) {
         E.label_props[prop].label0 = best;

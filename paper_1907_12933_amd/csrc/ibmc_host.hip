@@ -590,7 +590,8 @@ static ibmc_status build_f32(ibmc_ctx *ctx, ibmc_mlp *m) {
             IBMC_TRY(m->buf.emplace_back().upload(wp.data(), wp.size() * 4, s));
             f.WP[l] = (const float *)m->buf.back().p;
         }
-        std::vector<float> bp(hout, 0.f);
+        // (lane kernels: a class past the network's never wins)
+        std::vector<float> bp(hout, l == m->L && f.kind == F32_LANE ? -INFINITY : 0.f);
         for (int j = 0; j < nout; ++j) bp[j] = m->bf[l - 1][j];
         IBMC_TRY(m->buf.emplace_back().upload(bp.data(), bp.size() * 4, s));
         f.bP[l] = (const float *)m->buf.back().p;

@@ -83,7 +83,8 @@ struct FNetDev {
     const float *Wd[kMaxLayers + 1];   // l >= 1: row-major [dims[l]][dims[l-1]]
     const float *bd[kMaxLayers + 1];
     // enumeration layout: widths padded to HP (zero weights and biases in the
-    // padding, whose units therefore add exact zeros downstream)
+    // padding, whose units therefore add exact zeros downstream; the lane
+    // kinds' padded classes have a bias of -infinity)
     int kind;                          // F32Kind
     int HP[kMaxLayers + 1];            // HP[0] = pixels
     const float *W1P;                  // [n][HP1] transposed first layer
