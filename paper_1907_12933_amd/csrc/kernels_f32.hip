@@ -72,7 +72,7 @@ __global__ void __launch_bounds__(256) forward_f32_kernel(FNetDev net, const uin
 // loads' latency, so a block of kU0Block weights is on its way while the one
 // before is summed, and a workgroup holds 64 units of one property: eight
 // properties took 120 us with one load in flight (the mean over eight networks
-of 35 to 784 pixels), now 23 us.
+// of 35 to 784 pixels), now 23 us.
 constexpr int kU0Block = 32;
 
 __device__ __forceinline__ void u0_loads(const float *w, int h1, int i0, int n, float (&v)[kU0Block]) {
