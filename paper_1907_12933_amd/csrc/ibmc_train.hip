@@ -20,9 +20,10 @@ using namespace ibmc;
 namespace {
 
 // Samples of one pass at most: its rows of activations and deltas take up to
-// 256 MiB.
-int64_t pass_cap(const TrainNetDev &N) {
-    return std::max<int64_t>(kTrainTile, (256ll << 20) / (8ll * N.units) / kTrainTile * kTrainTile);
+// 256 MiB; whole workgroups and whole groups.
+int64_t pass_cap(const TrainNetDev &N, int group) {
+    const int64_t unit = kTrainTile * group;
+    return std::max<int64_t>(unit, (256ll << 20) / (8ll * N.units) / unit * unit);
 }
 
 ibmc_status check_train_args(ibmc_ctx *ctx, const ibmc_mlp *net, const uint8_t *images, const int32_t *labels,
@@ -66,8 +67,8 @@ void shuffle_epoch(uint64_t seed, int epoch, std::vector<int64_t> &ord) {
 
 // Buffers of passes of up to `count` samples, carved from one allocation.
 ibmc_status reserve_pass(const TrainNetDev &N, int64_t count, DevBuf &buf, TrainPassParams &P) {
-    const int64_t rows = (std::min(count, pass_cap(N)) + kTrainTile - 1) / kTrainTile * kTrainTile;
-    IBMC_TRY(buf.reserve((size_t)(2 * rows * N.units + rows / kTrainTile) * sizeof(float)));
+    const int64_t rows = (std::min(count, pass_cap(N, P.group)) + kTrainTile - 1) / kTrainTile * kTrainTile;
+    IBMC_TRY(buf.reserve((size_t)(2 * rows * N.units + rows) * sizeof(float)));
     P.net = N;
     P.acts = buf.as<float>();
     P.dels = P.acts + rows * N.units;
@@ -93,6 +94,7 @@ extern "C" ibmc_status ibmc_mlp_loss_grad(ibmc_ctx *ctx, const ibmc_mlp *net, co
     IBMC_TRY(dlab.upload(labels, (size_t)n * 4, s));
     IBMC_TRY(dgrad.reserve((size_t)N.n_params * 4));
     IBMC_TRY(dloss.reserve(8));
+    P.group = train_group(N, kTrainMaxGroup);
     IBMC_TRY(reserve_pass(N, n, rows, P));
     HIP_OK(launch_fill_u64(dloss.as<unsigned long long>(), 1, 0ull, s));
     P.theta = dth.as<float>();
@@ -103,7 +105,7 @@ extern "C" ibmc_status ibmc_mlp_loss_grad(ibmc_ctx *ctx, const ibmc_mlp *net, co
     U.grad = dgrad.as<float>();
     U.loss_acc = dloss.as<double>();
     for (P.e0 = 0; P.e0 < n; P.e0 += P.count) {
-        P.count = std::min<int64_t>(n - P.e0, pass_cap(N));
+        P.count = std::min<int64_t>(n - P.e0, pass_cap(N, P.group));
         U.accumulate = P.e0 > 0;
         HIP_OK(launch_train_pass(P, s));
         HIP_OK(launch_train_weights(P, U, s));
@@ -147,9 +149,10 @@ extern "C" ibmc_status ibmc_fit_mlp(ibmc_ctx *ctx, const ibmc_mlp *net, const ui
     IBMC_TRY(dlab.upload(labels, (size_t)n * 4, s));
     IBMC_TRY(dord.reserve((size_t)n * 8));
     IBMC_TRY(dloss.reserve((size_t)o->epochs * 8));
+    P.group = train_group(N, (int)std::min<int64_t>(kTrainMaxGroup, (B + 31) / 32));
     IBMC_TRY(reserve_pass(N, B, rows, P));
     // a batch beyond one pass gathers its gradient before its step
-    const bool whole = B <= pass_cap(N);
+    const bool whole = B <= pass_cap(N, P.group);
     if (!whole) IBMC_TRY(dgrad.reserve((size_t)N.n_params * 4));
     HIP_OK(launch_fill_u64(dmom.as<unsigned long long>(), (N.n_params + 1) / 2, 0ull, s));
     HIP_OK(launch_fill_u64(dvel.as<unsigned long long>(), (N.n_params + 1) / 2, 0ull, s));
@@ -191,7 +194,7 @@ extern "C" ibmc_status ibmc_fit_mlp(ibmc_ctx *ctx, const ibmc_mlp *net, const ui
             TrainUpdate G = U;
             G.grad = dgrad.as<float>();
             for (; P.e0 < b0 + cnt; P.e0 += P.count) {
-                P.count = std::min<int64_t>(b0 + cnt - P.e0, pass_cap(N));
+                P.count = std::min<int64_t>(b0 + cnt - P.e0, pass_cap(N, P.group));
                 G.accumulate = P.e0 > b0;
                 HIP_OK(launch_train_pass(P, s));
                 HIP_OK(launch_train_weights(P, G, s));

@@ -9,8 +9,8 @@
 
 namespace ibmc {
 
-constexpr int kTrainThreads = 1024;
 constexpr int kTrainTile = 4;              // samples per workgroup of the pass
+constexpr int kTrainMaxGroup = 16;         // samples per running sum (train_group)
 
 // The flat parameter vector theta: for each layer l = 1..L in turn, W_l
 // row-major [dims[l]][dims[l-1]] then b_l [dims[l]].
@@ -28,8 +28,14 @@ struct TrainNetDev {
 
 TrainNetDev train_layout(int L, const int *dims);
 
+// Samples per running sum: a gradient entry is the sum, in sample order, of
+// the sums over groups of this many samples (and so is the loss).  At most
+// `wanted`, and fewer for wide networks.  Part of the results' definition:
+// another group rounds otherwise.
+int train_group(const TrainNetDev &N, int wanted);
+
 // One pass over elements e0 .. e0 + count - 1: rows of activations and deltas
-// (count padded to kTrainTile rows) and one loss sum per workgroup.
+// (count padded to kTrainTile rows) and each sample's loss.
 struct TrainPassParams {
     TrainNetDev net;
     const float *theta;
@@ -39,7 +45,8 @@ struct TrainPassParams {
     int64_t e0, count;
     float inv_n;               // 1 / the number of samples the mean runs over
     float *acts, *dels;        // [rows][units]
-    float *loss;               // [ceil(count / kTrainTile)]
+    float *loss;               // [count]
+    int group;                 // samples per running sum
 };
 
 // What becomes of the weight gradients of a pass.
