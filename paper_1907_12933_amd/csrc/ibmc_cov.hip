@@ -97,8 +97,7 @@ static ibmc_status cov_finish(ibmc_ctx *ctx, CovRun &R, int first_crit, int n_cr
     const int64_t words = (R.lay.total_pairs + 63) / 64;
     if (covered_bits && words > 0) {
         IBMC_TRY(ctx->cov_out.reserve((size_t)words * 8 * n_crit));
-        for (int c = 0; c < n_crit; ++c)
-            HIP_OK(launch_cov_expand(R.lay, R.bits, first_crit + c, ctx->cov_out.as<uint64_t>() + c * words, words, s));
+        HIP_OK(launch_cov_expand(R.lay, R.bits, first_crit, n_crit, ctx->cov_out.as<uint64_t>(), words, s));
     }
     HIP_OK(hipEventRecord(ctx->ev1, s));
     unsigned long long h[8];
@@ -160,6 +159,10 @@ static ibmc_status coverage_impl(ibmc_ctx *ctx, const ibmc_mlp *net, const uint8
         cpp.x1 = d1;
         cpp.x2 = d2;
         cpp.n_pairs = n_pairs;
+        for (int l = 1; l <= net->L; ++l)
+            if (net->pot_bound[l] < (1LL << 24) && std::max(cp.ratio_num, cp.ratio_den) < (1 << 24) &&
+                net->pot_bound[l] * std::max(cp.ratio_num, cp.ratio_den) < (1LL << 32))
+                cpp.small |= 1u << l;
         HIP_OK(launch_cov_pair(cpp, ctx->n_cu, s));
     }
     if (!on_device) HIP_OK(hipStreamSynchronize(s));  // host images may be released after return

@@ -150,6 +150,7 @@ struct ibmc_mlp {
     ibmc::FwdExtra fx;
     ibmc::FNetDev fd;
     ibmc::LaneNetDev lane{};           // integer nets the lane kernels serve (lane.ok)
+    int64_t pot_bound[IBMC_MAX_LAYERS + 1] = {};  // integer nets: no potential of layer l is larger in magnitude
     bool fold_ok = false;              // integer nets whose properties may be folded
     bool fold_joint = false;           // their first two layers hold no weight of -128
     std::string forced_variant;

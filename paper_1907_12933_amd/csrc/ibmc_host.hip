@@ -648,6 +648,7 @@ extern "C" ibmc_status ibmc_load_mlp(ibmc_ctx *ctx, const ibmc_mlp_desc *d, ibmc
             for (int j = 0; j < nout; ++j) {
                 int64_t s = std::llabs((long long)b[j]) + off;
                 for (int i = 0; i < nin; ++i) s += std::llabs((long long)W[(size_t)j * nin + i]) * amax;
+                m->pot_bound[l + 1] = std::max(m->pot_bound[l + 1], s);
                 if (s >= (1LL << 31))
                     return fail(IBMC_E_RANGE, "layer %d neuron %d: accumulator bound %lld reaches 2^31", l + 1, j,
                                 (long long)s);

@@ -48,8 +48,7 @@ struct CovSums {
     int64_t colmask_stride;
 };
 
-// One pass over input pairs: forward of both images on int8 MFMA (x2's first
-// layer as the rank-r update of x1's), the per-neuron tests and the covered
+// One pass over input pairs: forward of both images on int8 MFMA, the per-neuron tests and the covered
 // rows, with no potentials in memory.  x1 / x2: device [n_pairs][dims[0]].
 struct CovPairParams {
     QNetDev net;
@@ -59,9 +58,12 @@ struct CovPairParams {
     CovBits bits;
     const uint8_t *x1, *x2;
     int64_t n_pairs;
+    // layers (bit l) whose potentials are below 2^24 and, times the ratio's
+    // terms, below 2^32: their tests take 24-bit products
+    uint32_t small;
     // LDS plan (cov_pair_plan): activation row stride, per-pair nibble
     // offsets of each layer, byte offsets of the regions
-    int act_stride, nib_stride, off_nib, off_dist, off_diff, off_all;
+    int act_stride, nib_stride, off_nib, off_dist, off_all;
     int nib_off[kMaxLayers + 2];
 };
 
@@ -72,7 +74,8 @@ hipError_t launch_fwd_pots_q8(const QNetDev &net, const FwdExtra &fx, const uint
 hipError_t launch_cov_pred_i64(const int64_t *p1, const int64_t *p2, int64_t n_pairs, const CovLayout &lay,
                                const CovParams &cp, const CovBits &bits, hipStream_t s);
 hipError_t launch_cov_summary(const CovLayout &lay, const CovBits &bits, const CovSums &sums, hipStream_t s);
-hipError_t launch_cov_expand(const CovLayout &lay, const CovBits &bits, int crit, uint64_t *out, int64_t n_words,
-                             hipStream_t s);
+// The covered pairs of n_crit criteria in the caller's layout, n_words each.
+hipError_t launch_cov_expand(const CovLayout &lay, const CovBits &bits, int first_crit, int n_crit, uint64_t *out,
+                             int64_t n_words, hipStream_t s);
 
 }  // namespace ibmc
