@@ -102,31 +102,10 @@ __device__ __forceinline__ unsigned lane_rank(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
-// Counterexample and near-tie records of one wave's points: one atomic per
-// wave and kind for the slots, one for the level counter; lanes write their
-// own records at base + their rank among the set lanes.
-__device__ __forceinline__ void emit_f32(const FEnumParams &P, const Cursor &c, bool viol, bool near, int p, int i,
-                                         int best) {
+// The near ties among one wave's points.
+__device__ __forceinline__ void emit_near(const FEnumParams &P, const Cursor &c, bool near, int p, int i, int best) {
     const int lane = __lane_id();
-    const unsigned long long mv = __ballot(viol), mn = __ballot(near);
-    if (mv) {
-        unsigned long long base = 0;
-        if (lane == 0) {
-            base = atomicAdd(P.rec_count, (unsigned long long)__popcll(mv));
-            atomicAdd(P.slot_cex + c.slot, (unsigned long long)__popcll(mv));
-        }
-        base = wave_uniform(base);
-        if (viol) {
-            const unsigned long long idx = base + lane_rank(mv);
-            if ((int64_t)idx < P.rec_cap) {
-                DevRec r;
-                r.rank = point_rank<FEnumParams>(c, P, p, i);
-                r.prop = c.prop;
-                r.klab = (c.k << 24) | best;
-                P.recs[idx] = r;
-            }
-        }
-    }
+    const unsigned long long mn = __ballot(near);
     if (mn) {
         unsigned long long base = 0;
         if (lane == 0) {
@@ -145,6 +124,34 @@ __device__ __forceinline__ void emit_f32(const FEnumParams &P, const Cursor &c, 
             }
         }
     }
+}
+
+// Counterexample and near-tie records of one wave's points: one atomic per
+// wave and kind for the slots, one for the level counter; lanes write their
+// own records at base + their rank among the set lanes.
+__device__ __forceinline__ void emit_f32(const FEnumParams &P, const Cursor &c, bool viol, bool near, int p, int i,
+                                         int best) {
+    const int lane = __lane_id();
+    const unsigned long long mv = __ballot(viol);
+    if (mv) {
+        unsigned long long base = 0;
+        if (lane == 0) {
+            base = atomicAdd(P.rec_count, (unsigned long long)__popcll(mv));
+            atomicAdd(P.slot_cex + c.slot, (unsigned long long)__popcll(mv));
+        }
+        base = wave_uniform(base);
+        if (viol) {
+            const unsigned long long idx = base + lane_rank(mv);
+            if ((int64_t)idx < P.rec_cap) {
+                DevRec r;
+                r.rank = point_rank<FEnumParams>(c, P, p, i);
+                r.prop = c.prop;
+                r.klab = (c.k << 24) | best;
+                P.recs[idx] = r;
+            }
+        }
+    }
+    emit_near(P, c, near, p, i, best);
 }
 
 // Tickets between two reads of the host's abort request by one wave (a read
@@ -212,6 +219,117 @@ __device__ __forceinline__ void decode_point_dev(int n, int m, int k, int64_t ra
 // ---------------------------------------------------------------------------
 
 constexpr int kLaneWaves = 4;  // waves per workgroup of the lane kernels
+
+// A wave's position for the lane kernels.  The whole cursor lives in the
+// wave's LDS; the fields that a chunk needs are kept as scalars.  (All of it in
+// registers, with the code that moves it inlined around the point's own work,
+// took 182 vector registers for sixteen units, two waves a SIMD, or spilled.)
+// These kernels take plain jobs only (SEG_PLAIN).
+struct LaneCursor {
+    Cursor *S;
+    int q, m, seglen, ch, nch, prop, slot, k;
+    unsigned mmagic, m1;
+    const uint8_t *img;
+    const int16_t *dl;
+    __device__ __forceinline__ void refresh() {
+        ranked = false;
+        q = wave_uniform(S->q);
+        m = wave_uniform(S->m);
+        seglen = wave_uniform((int)S->seglen);
+        ch = wave_uniform((int)S->ch);
+        nch = wave_uniform((int)S->nch);
+        prop = wave_uniform(S->prop);
+        slot = wave_uniform(S->slot);
+        k = wave_uniform(S->k);
+        mmagic = (unsigned)wave_uniform((int)S->mmagic);
+        m1 = (unsigned)wave_uniform((int)S->m1);
+        img = reinterpret_cast<const uint8_t *>(wave_uniform((unsigned long long)S->img));
+        dl = reinterpret_cast<const int16_t *>(wave_uniform((unsigned long long)S->dl));
+    }
+    template <int CH, class PT>
+    __device__ __forceinline__ void decode(const PT &P, int64_t chunk) {
+        Cursor c;
+        cursor_decode<CH, PT>(c, P, chunk);
+        *S = c;
+        refresh();
+    }
+    // To chunk `chunk`, the next one; true when the segment changed.
+    template <int CH, class PT>
+    __device__ __forceinline__ bool next(const PT &P, int64_t chunk) {
+        if (++ch < nch) return false;
+        Cursor c = *S;
+        c.mode = SEG_PLAIN;
+        c.ch = c.nch - 1;
+        c.chunk = chunk - 1;
+        cursor_next<CH, PT>(c, P);
+        *S = c;
+        refresh();
+        return true;
+    }
+    // last_element32
+    __device__ __forceinline__ bool last_element(int o, int &p, int &i) const {
+        const bool ok = o < seglen;
+        const unsigned uo = ok ? (unsigned)o : 0u;
+        const unsigned qd = __umulhi(uo, mmagic) + uo * m1;
+        p = q + 1 + (int)qd;
+        i = (int)(uo - qd * (unsigned)m);
+        return ok;
+    }
+    // A point's rank is linear in its last pixel and delta: r0 + p mk + i, r0 of
+    // the segment worked out at its first record.
+    int64_t r0, mk;
+    bool ranked;
+    template <class PT>
+    __device__ __forceinline__ int64_t rank(const PT &P, int p, int i) {
+        if (!ranked) {
+            Cursor c = *S;
+            c.mode = SEG_PLAIN;
+            mk = 1;
+            for (int j = 0; j < k; ++j) mk *= m;
+            const int64_t first = point_rank<PT>(c, P, q + 1, 0) - (int64_t)(q + 1) * mk;
+            r0 = (int64_t)wave_uniform((unsigned long long)first);
+            ranked = true;
+        }
+        return r0 + (int64_t)p * mk + i;
+    }
+};
+
+// The wave's records, gathered in LDS: one atomic on the call's record count
+// and one coalesced store per 65 records or more.  An atomic per chunk made
+// every wave wait for the one address: ten glyphs' L2 balls (27 million points,
+// 1.8 million records) took 3.4 ms; with this, the skipped prefixes, longer
+// tickets and the matrix cores 1.5.
+constexpr int kLaneRecs = 128;
+
+struct LaneRecords {
+    DevRec *buf;   // [kLaneRecs]
+    int n;         // (wave-uniform)
+    // the records of the lanes in mask, mine among them (viol)
+    template <class PT>
+    __device__ __forceinline__ void put(const PT &P, unsigned long long mask, bool viol, int64_t rank, int prop, int klab,
+                                        int lane) {
+        if (viol) {
+            DevRec r;
+            r.rank = rank;
+            r.prop = prop;
+            r.klab = klab;
+            buf[n + lane_rank(mask)] = r;
+        }
+        n += __popcll(mask);
+        if (n > kLaneRecs - 64) flush(P, lane);
+    }
+    template <class PT>
+    __device__ __forceinline__ void flush(const PT &P, int lane) {
+        unsigned long long rb = 0;
+        if (lane == 0) rb = atomicAdd(P.rec_count, (unsigned long long)n);
+        rb = wave_uniform(rb);
+        wave_lds_sync();
+        for (int t = lane; t < n; t += 64)
+            if ((int64_t)(rb + t) < P.rec_cap) P.recs[rb + t] = buf[t];
+        wave_lds_sync();
+        n = 0;
+    }
+};
 
 // One layer of the lanes' points on the matrix cores: the 4x4x1 FP32 product
 // of sixteen blocks gives every lane, from its own activation (B: point
@@ -379,7 +497,17 @@ __global__ void __launch_bounds__(256, H1 <= 16 ? 4 : H1 <= 32 ? 3 : 2) enum_f32
     const int nc = P.net.dims[P.net.L];
     LaneOut<H1, H2, NCP> out;
     out.load(P.net, lane);
-    Cursor c;
+    __shared__ __attribute__((aligned(16))) DevRec rbuf[kLaneWaves][kLaneRecs];
+    __shared__ __attribute__((aligned(16))) Cursor cursors[kLaneWaves];
+    LaneRecords recs{&rbuf[threadIdx.x >> 6][0], 0};
+    LaneCursor c;
+    c.S = &cursors[threadIdx.x >> 6];
+    int tslot = -1;
+    unsigned long long tcex = 0;
+    auto tally = [&]() __attribute__((always_inline)) {
+        if (tcex && lane == 0) atomicAdd(P.slot_cex + tslot, tcex);
+        tcex = 0;
+    };
     int64_t cur = 0, end = 0;
     bool seg_new = true;
     int prop_seen = -1, label0 = 0;
@@ -389,12 +517,16 @@ __global__ void __launch_bounds__(256, H1 <= 16 ? 4 : H1 <= 32 ? 3 : 2) enum_f32
             const int64_t start = f32_ticket(P, q, tries, end, polls);
             if (start < 0) break;
             cur = start;
-            cursor_decode<CH, FEnumParams>(c, P, cur);
+            c.decode<CH, FEnumParams>(P, cur);
             seg_new = true;
+        }
+        if (c.slot != tslot) {
+            tally();
+            tslot = c.slot;
         }
         // the lane's point: its loads go out first
         int p = 0, i = 0;
-        const bool valid = last_element32<FEnumParams>(c, P, (int)(c.ch * CH) + lane, p, i);
+        const bool valid = c.last_element(c.ch * CH + lane, p, i);
         const int xv = gld(c.img + p), dv = gld(c.dl + i);
         float4 wrow[H1 / 4];
         const float4 *w1 = reinterpret_cast<const float4 *>(P.net.W1P + (int64_t)p * H1);
@@ -407,7 +539,7 @@ __global__ void __launch_bounds__(256, H1 <= 16 ? 4 : H1 <= 32 ? 3 : 2) enum_f32
         if (seg_new) {
             int pp[kMaxK];
             float ee[kMaxK];
-            segment_prefix(c, pp, ee);
+            segment_prefix(*c.S, pp, ee);
             const float *u0 = P.u0f + (int64_t)c.prop * P.u0_stride;
 #pragma unroll
             for (int j0 = 0; j0 < H1; j0 += 64)
@@ -446,10 +578,17 @@ __global__ void __launch_bounds__(256, H1 <= 16 ? 4 : H1 <= 32 ? 3 : 2) enum_f32
             viol = valid && zd < V && other > V;
             near = valid && fminf(fabsf(zd - V), fabsf(other - V)) <= P.tie_rel * fmaxf(1.0f, fabsf(V));
         }
-        emit_f32(P, c, viol, near, p, i, best);
+        const unsigned long long mv = __ballot(viol);
+        if (mv) {
+            tcex += (unsigned long long)__popcll(mv);
+            recs.put(P, mv, viol, c.rank<FEnumParams>(P, p, i), c.prop, (c.k << 24) | best, lane);
+        }
+        if (__ballot(near)) emit_near(P, *c.S, near, p, i, best);
         cur++;
-        if (cur < end) seg_new = cursor_next<CH, FEnumParams>(c, P);
+        if (cur < end) seg_new = c.next<CH, FEnumParams>(P, cur);
     }
+    tally();
+    if (recs.n) recs.flush(P, lane);
 }
 
 // Listed points (or the clean images of listed properties), one per lane,

@@ -306,7 +306,9 @@ static ibmc_status build_lane(ibmc_mlp *m, hipStream_t s) {
         IBMC_TRY(m->buf.emplace_back().upload(b2.data(), b2.size() * 4, s));
         ln.b2 = (const int32_t *)m->buf.back().p;
     }
-    const std::vector<int32_t> wo = words(m->Wq[L - 1], nc, hl, 16, HL), bo = padded(m->bq[L - 1], nc, 16);
+    const std::vector<int32_t> wo = words(m->Wq[L - 1], nc, hl, 16, HL);
+    std::vector<int32_t> bo(16, INT32_MIN);   // (a class past the network's never wins)
+    for (int j = 0; j < nc; ++j) bo[j] = m->bq[L - 1][j];
     IBMC_TRY(m->buf.emplace_back().upload(wo.data(), wo.size() * 4, s));
     ln.WOS = (const int32_t *)m->buf.back().p;
     IBMC_TRY(m->buf.emplace_back().upload(bo.data(), bo.size() * 4, s));

@@ -145,7 +145,7 @@ struct LaneNetDev {
                                        // 4w..4w+3 of unit 8s + t)
     const int32_t *b2;                 // L == 3: [LH2]
     const int32_t *WOS;                // [2][LHL / 4][8] output words, LHL the last hidden width
-    const int32_t *bo;                 // [16]
+    const int32_t *bo;                 // [16], the lowest value past the network's classes
 };
 
 // Ordering of the last perturbed element inside a segment.
