@@ -269,11 +269,11 @@ extern "C" ibmc_status ibmc_coverage_search(ibmc_ctx *ctx, const ibmc_mlp *net, 
     HIP_OK(hipMemcpyAsync(dimg, image, (size_t)n, hipMemcpyHostToDevice, s));
     HIP_OK(hipMemcpyAsync(ddel, delta_set, (size_t)n_deltas * 2, hipMemcpyHostToDevice, s));
     const size_t mask_bytes = (size_t)nc * words * 8;
-    // [potentials | masks | labels | covered (kCovSearchMaxWords words) | a batch of greedy steps' best
-    // keys | their labels], 256-byte aligned parts
+    // [potentials | masks | labels | covered (kCovSearchMaxWords words) before each step of a batch | the
+    // steps' best keys | their labels], 256-byte aligned parts
     constexpr int kSteps = 16;
     const size_t need = ((size_t)lay.U * 4 + 255) / 256 * 256 + (mask_bytes + 255) / 256 * 256 +
-                        ((size_t)nc * 4 + 255) / 256 * 256 + (size_t)(kCovSearchMaxWords + kSteps) * 8 +
+                        ((size_t)nc * 4 + 255) / 256 * 256 + (size_t)(kSteps * kCovSearchMaxWords + kSteps) * 8 +
                         (size_t)kSteps * 4;
     IBMC_TRY(ctx->cov_pots.reserve(need));
     char *base = ctx->cov_pots.as<char>();
@@ -282,7 +282,7 @@ extern "C" ibmc_status ibmc_coverage_search(ibmc_ctx *ctx, const ibmc_mlp *net, 
     int32_t *labels = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(masks) + ((mask_bytes + 255) / 256) * 256);
     unsigned long long *covered =
         reinterpret_cast<unsigned long long *>(reinterpret_cast<char *>(labels) + (((size_t)nc * 4 + 255) / 256) * 256);
-    unsigned long long *keys = covered + kCovSearchMaxWords;
+    unsigned long long *keys = covered + kSteps * kCovSearchMaxWords;
     int32_t *labs = reinterpret_cast<int32_t *>(keys + kSteps);
     HIP_OK(launch_fwd_pots_q8(net->qd, net->fx, dimg, 1, pot0, lay.U, nullptr, s));
     CovCandParams cpar{};
@@ -314,10 +314,13 @@ extern "C" ibmc_status ibmc_coverage_search(ibmc_ctx *ctx, const ibmc_mlp *net, 
     while (taken < max_tests && !done) {
         const int nb = std::min(kSteps, max_tests - taken);
         HIP_OK(launch_fill_u64(keys, nb, 0ull, s));
-        for (int i = 0; i < nb; ++i) {
-            HIP_OK(launch_cov_gain(masks, nc, words, covered, keys + i, s));
-            HIP_OK(launch_cov_take(masks, words, keys + i, covered, labels, labs + i, s));
-        }
+        // step i adds winner i - 1 to the covered set; the last one goes back to the
+        // set before the first step
+        auto before = [&](int i) { return covered + (size_t)i * kCovSearchMaxWords; };
+        HIP_OK(launch_cov_step(masks, nc, words, before(0), nullptr, nullptr, labels, nullptr, keys, s));
+        for (int i = 1; i < nb; ++i)
+            HIP_OK(launch_cov_step(masks, nc, words, before(i - 1), keys + i - 1, before(i), labels, labs + i - 1, keys + i, s));
+        HIP_OK(launch_cov_step(masks, nc, words, before(nb - 1), keys + nb - 1, before(0), labels, labs + nb - 1, nullptr, s));
         HIP_OK(hipMemcpyAsync(hk, keys, (size_t)nb * 8, hipMemcpyDeviceToHost, s));
         HIP_OK(hipMemcpyAsync(hl, labs, (size_t)nb * 4, hipMemcpyDeviceToHost, s));
         HIP_OK(hipStreamSynchronize(s));

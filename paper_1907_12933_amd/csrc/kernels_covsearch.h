@@ -22,10 +22,12 @@ struct CovCandParams {
 };
 
 hipError_t launch_cov_cand(const CovCandParams &P, hipStream_t s);
-hipError_t launch_cov_gain(const unsigned long long *masks, int64_t n_cand, int words,
-                           const unsigned long long *covered, unsigned long long *best_key, hipStream_t s);
-// ORs the winner's bits into `covered` and writes its label (-1: no winner).
-hipError_t launch_cov_take(const unsigned long long *masks, int words, const unsigned long long *best_key,
-                           unsigned long long *covered, const int32_t *labels, int32_t *label_out, hipStream_t s);
+// One greedy step: the best candidate beyond `prev` and (prev_key non-null) the
+// last step's winner, whose label goes to prev_label (-1: none) and whose sum
+// with prev to `next`, which must be another buffer.  best_key null: only that
+// (and next may be prev).
+hipError_t launch_cov_step(const unsigned long long *masks, int64_t n_cand, int words, const unsigned long long *prev,
+                           const unsigned long long *prev_key, unsigned long long *next, const int32_t *labels,
+                           int32_t *prev_label, unsigned long long *best_key, hipStream_t s);
 
 }  // namespace ibmc

@@ -10,24 +10,79 @@
 // covering the most pairs not yet covered (the host queues the steps in
 // batches and reads their winners back once per batch).  Networks whose non-input layers
 // have at most 64 units (one lane per unit).
+#include <climits>
+
 #include "kernels_covsearch.h"
 #include "enum_common.h"
 
 namespace ibmc {
 
+// lex_unrank_subset by a wave: the values of one element side by side, where
+// one after another, two 64-bit divisions each, they took most of the kernel.
+__device__ __forceinline__ void wave_unrank_subset(int64_t rank, int k, int n, int lane, int (&p)[kMaxK]) {
+    int64_t R = binom_small(n, k) - 1 - rank;
+    int c = n;
+#pragma unroll
+    for (int j = 0; j < kMaxK; ++j) {
+        if (j >= k) break;
+        const int r = k - j;
+        // the largest cj < c with binom(cj, r) <= R, or r - 1
+        int cj = r - 1;
+        int64_t bj = 0;
+        for (int base = r; base < c; base += 64) {
+            const int v = base + lane;
+            const int64_t b = binom_small(min(v, c - 1), r);
+            const int cnt = __popcll(__ballot(v < c && b <= R));
+            if (cnt == 0) break;
+            cj = base + cnt - 1;
+            bj = __shfl(b, cnt - 1);
+            if (cnt < 64) break;
+        }
+        R -= bj;
+        p[j] = n - 1 - cj;
+        c = cj;
+    }
+}
+
+// A wave keeps its unit's weights of layers 2 .. L in registers, packed for
+// four-way dot products, over all of its candidates; bound by latency (one wave
+// per candidate, a few thousand candidates).  With a byte load and a wait per
+// weight 3,915 candidates of 30-40-30-6 took 116 us, now 49 us
+// (the weights in registers alone changed nothing; the unranking below did).
 __global__ void __launch_bounds__(64) cov_cand_kernel(CovCandParams P) {
-    __shared__ int act[64];
+    __shared__ __attribute__((aligned(16))) int act[16];   // 64 activations, a byte each
     __shared__ unsigned long long mask[kCovSearchMaxWords];
     const int lane = threadIdx.x;
     const QNetDev &net = P.net;
     const int L = net.L, n = net.dims[0], m = P.m;
+    int wr[kMaxLayers - 1][16], br[kMaxLayers - 1];
+#pragma unroll
+    for (int l = 2; l <= kMaxLayers; ++l) {
+        br[l - 2] = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) wr[l - 2][w] = 0;
+        if (l > L) continue;
+        const int h = net.dims[l], hin = net.dims[l - 1], j = min(lane, h - 1);
+        br[l - 2] = net.bd[l][j];
+        const int8_t *row = net.Wd[l] + (int64_t)j * hin;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            uint32_t v = 0;
+#pragma unroll
+            for (int z = 0; z < 4; ++z) {
+                const int b = (uint8_t)row[min(4 * w + z, hin - 1)];
+                v |= (uint32_t)(4 * w + z < hin ? b : 0) << (8 * z);
+            }
+            wr[l - 2][w] = (int)v;
+        }
+    }
     for (int64_t c = blockIdx.x; c < P.n_cand; c += gridDim.x) {
         // the candidate's pixels and offsets (ascending pixels, digits base m)
         const int64_t rank = P.rank0 + c;
         int64_t mk = 1;
         for (int t = 0; t < P.k; ++t) mk *= m;
         int pix[kMaxK], off[kMaxK];
-        lex_unrank_subset(rank / mk, P.k, n, pix);
+        wave_unrank_subset(rank / mk, P.k, n, lane, pix);
         int64_t d = rank % mk;
         for (int t = P.k - 1; t >= 0; --t) {
             const int di = (int)(d % m);
@@ -40,19 +95,20 @@ __global__ void __launch_bounds__(64) cov_cand_kernel(CovCandParams P) {
         int dc[kMaxLayers];
         int label = 0;
         int uoff = 0;
-        for (int l = 1; l <= L; ++l) {
+#pragma unroll
+        for (int l = 1; l <= kMaxLayers; ++l) {
+            if (l > L) break;
             const int h = net.dims[l];
             int u = 0;
-            if (lane < h) {
-                if (l == 1) {
+            if (l == 1) {
+                if (lane < h) {
                     u = P.pot0[lane];
                     for (int t = 0; t < P.k; ++t) u += off[t] * (int)net.Wd[1][(int64_t)lane * n + pix[t]];
-                } else {
-                    const int hin = net.dims[l - 1];
-                    u = net.bd[l][lane];
-                    const int8_t *row = net.Wd[l] + (int64_t)lane * hin;
-                    for (int i = 0; i < hin; ++i) u += act[i] * (int)row[i];
                 }
+            } else {
+                u = br[l - 2];
+#pragma unroll
+                for (int w = 0; w < 16; ++w) u = __builtin_amdgcn_sdot4(act[w], wr[l - 2][w], u, false);
             }
             // changes against the clean image's potentials of this layer
             const int a = lane < h ? P.pot0[uoff + lane] : 0;
@@ -77,16 +133,18 @@ __global__ void __launch_bounds__(64) cov_cand_kernel(CovCandParams P) {
             // this layer's activations for the next one; the label from the last
             __syncthreads();
             if (l < L) {
-                if (lane < h) act[lane] = min(max(u >> net.shift[l - 1], 0), 127);
+                reinterpret_cast<int8_t *>(act)[lane] = lane < h ? (int8_t)min(max(u >> net.shift[l - 1], 0), 127) : (int8_t)0;
             } else {
-                if (lane < h) act[lane] = u;
+                // lowest-index argmax
+                long long key = lane < h ? ((long long)u << 6) | (63 - lane) : LLONG_MIN;
+#pragma unroll
+                for (int sh = 32; sh >= 1; sh >>= 1) {
+                    const long long o = __shfl_xor(key, sh);
+                    key = o > key ? o : key;
+                }
+                label = 63 - (int)(key & 63);
             }
             __syncthreads();
-            if (l == L && lane == 0) {
-                int best = 0;
-                for (int j = 1; j < h; ++j) if (act[j] > act[best]) best = j;
-                label = best;
-            }
         }
         // covered pairs: block l pairs layer l (rows i) with layer l + 1
         int64_t boff = 0;
@@ -113,15 +171,30 @@ __global__ void __launch_bounds__(64) cov_cand_kernel(CovCandParams P) {
     }
 }
 
-// Gain of every candidate (pairs it covers beyond `covered`), reduced to
-// the largest gain, lowest candidate index first: key = gain 2^40 + (2^40 -
-// 1 - index).
-__global__ void __launch_bounds__(256) cov_gain_kernel(const unsigned long long *masks, int64_t n_cand, int words,
-                                                       const unsigned long long *covered,
-                                                       unsigned long long *best_key) {
+// The candidate of a key.
+__device__ __forceinline__ unsigned long long cov_key_index(unsigned long long key) {
+    return ((1ull << 40) - 1ull) - (key & ((1ull << 40) - 1ull));
+}
+
+// One greedy step: the gain of every candidate (pairs it covers beyond the
+// covered ones), reduced to the largest gain, lowest candidate index first: key
+// = gain 2^40 + (2^40 - 1 - index).  prev: the last step's covered set; with
+// prev_key, that step's winner is added to it first, by every workgroup for
+// itself, and the first one writes the sum (next) and the winner's label (-1:
+// no winner).  A launch of its own for that took 2.3 us a step and its gap.
+__global__ void __launch_bounds__(256) cov_step_kernel(const unsigned long long *masks, int64_t n_cand, int words,
+                                                       const unsigned long long *prev, const unsigned long long *prev_key,
+                                                       unsigned long long *next, const int32_t *labels,
+                                                       int32_t *prev_label, unsigned long long *best_key) {
     __shared__ unsigned long long cov[kCovSearchMaxWords];
     __shared__ unsigned long long red[4];
-    for (int w = threadIdx.x; w < words; w += blockDim.x) cov[w] = covered[w];
+    const unsigned long long last = prev_key ? *prev_key : 0ull;
+    for (int w = threadIdx.x; w < words; w += blockDim.x) {
+        cov[w] = prev[w] | (last ? masks[cov_key_index(last) * words + w] : 0ull);
+        if (prev_key && blockIdx.x == 0) next[w] = cov[w];
+    }
+    if (prev_key && blockIdx.x == 0 && threadIdx.x == 0) *prev_label = last ? labels[cov_key_index(last)] : -1;
+    if (!best_key) return;
     __syncthreads();
     unsigned long long key = 0;
     for (int64_t c = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; c < n_cand;
@@ -145,35 +218,19 @@ __global__ void __launch_bounds__(256) cov_gain_kernel(const unsigned long long 
     }
 }
 
-__global__ void cov_take_kernel(const unsigned long long *masks, int words, const unsigned long long *best_key,
-                                unsigned long long *covered, const int32_t *labels, int32_t *label_out) {
-    const unsigned long long key = *best_key;
-    if (!key) {
-        if (threadIdx.x == 0) *label_out = -1;
-        return;
-    }
-    const int64_t c = (int64_t)(((1ull << 40) - 1ull) - (key & ((1ull << 40) - 1ull)));
-    for (int w = threadIdx.x; w < words; w += blockDim.x) covered[w] |= masks[c * words + w];
-    if (threadIdx.x == 0) *label_out = labels[c];
-}
-
 hipError_t launch_cov_cand(const CovCandParams &P, hipStream_t s) {
     if (P.n_cand <= 0) return hipSuccess;
-    const int grid = (int)std::min<int64_t>(P.n_cand, 16384);
+    const int grid = (int)std::min<int64_t>(P.n_cand, 4096);
     hipLaunchKernelGGL(cov_cand_kernel, dim3(grid), dim3(64), 0, s, P);
     return hipGetLastError();
 }
 
-hipError_t launch_cov_gain(const unsigned long long *masks, int64_t n_cand, int words,
-                           const unsigned long long *covered, unsigned long long *best_key, hipStream_t s) {
-    const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((n_cand + 255) / 256, 2048));
-    hipLaunchKernelGGL(cov_gain_kernel, dim3(grid), dim3(256), 0, s, masks, n_cand, words, covered, best_key);
-    return hipGetLastError();
-}
-
-hipError_t launch_cov_take(const unsigned long long *masks, int words, const unsigned long long *best_key,
-                           unsigned long long *covered, const int32_t *labels, int32_t *label_out, hipStream_t s) {
-    hipLaunchKernelGGL(cov_take_kernel, dim3(1), dim3(64), 0, s, masks, words, best_key, covered, labels, label_out);
+hipError_t launch_cov_step(const unsigned long long *masks, int64_t n_cand, int words, const unsigned long long *prev,
+                           const unsigned long long *prev_key, unsigned long long *next, const int32_t *labels,
+                           int32_t *prev_label, unsigned long long *best_key, hipStream_t s) {
+    const int grid = best_key ? (int)std::max<int64_t>(1, std::min<int64_t>((n_cand + 255) / 256, 2048)) : 1;
+    hipLaunchKernelGGL(cov_step_kernel, dim3(grid), dim3(256), 0, s, masks, n_cand, words, prev, prev_key, next, labels,
+                       prev_label, best_key);
     return hipGetLastError();
 }
 
