@@ -1500,7 +1500,7 @@ ibmc_status check_batch_impl(ibmc_ctx *ctx, const ibmc_property *props, int32_t 
                              const int64_t *ball_r2) {
     clear_error();
     if (!ctx || !outs) return fail(IBMC_E_INVALID, "null ctx / outs");
-    IBMC_TRY(ctx->pin.reset());
+    ctx->pin.reset();
     const ibmc_status st = check_batch_run(ctx, props, n_props, o, outs, cex_buf, tie_buf, images_on_device, ball_r2);
     // an early return may leave copies from the pinned pieces in flight
     if (st < 0 && st != IBMC_E_ABORTED) (void)hipStreamSynchronize(ctx->stream);

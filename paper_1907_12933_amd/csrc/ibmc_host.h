@@ -78,14 +78,20 @@ struct DevBuf {
 // order and stay valid until the next call's reset (a call returns with its
 // stream idle).  Copies from and to it queue without a wait on the host.
 struct PinPool {
-    std::vector<std::pair<char *, size_t>> blocks;   // the last one is being carved
+    static constexpr size_t kPinKeep = (size_t)64 << 20;   // more is given back before the next call
+    struct Block {
+        char *p;
+        size_t size;
+        bool pinned;
+    };
+    std::vector<Block> blocks;                       // the last one is being carved
     size_t used = 0;
     PinPool() = default;
     PinPool(const PinPool &) = delete;
     PinPool &operator=(const PinPool &) = delete;
     ~PinPool();
     ibmc_status take(size_t n, void **out);          // 256-byte aligned
-    ibmc_status reset();                             // several blocks become one of their total size
+    void reset();                                    // several blocks become one of their total size
 };
 
 }  // namespace ibmc

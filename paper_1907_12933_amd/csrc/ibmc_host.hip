@@ -91,39 +91,48 @@ ibmc_status DevBuf::upload(const void *src, size_t n, hipStream_t s) {
     return IBMC_OK;
 }
 
+static void pin_free(const PinPool::Block &b) {
+    if (b.pinned) (void)hipHostFree(b.p);
+    else std::free(b.p);
+}
+
 PinPool::~PinPool() {
-    for (auto &b : blocks) (void)hipHostFree(b.first);
+    for (auto &b : blocks) pin_free(b);
 }
 
 ibmc_status PinPool::take(size_t n, void **out) {
     const size_t need = (std::max<size_t>(n, 1) + 255) & ~(size_t)255;
-    if (blocks.empty() || blocks.back().second - used < need) {
+    if (blocks.empty() || blocks.back().size - used < need) {
         const size_t size = std::max<size_t>(need, (size_t)256 << 10);
         void *p = nullptr;
-        if (hipHostMalloc(&p, size, hipHostMallocDefault) != hipSuccess)
-            return fail(IBMC_E_OOM, "hipHostMalloc(%zu) failed", size);
-        blocks.emplace_back((char *)p, size);
+        bool pinned = true;
+        if (hipHostMalloc(&p, size, hipHostMallocDefault) != hipSuccess) {
+            // pageable memory does, more slowly
+            (void)hipGetLastError();
+            pinned = false;
+            p = std::aligned_alloc(256, (size + 255) & ~(size_t)255);
+            if (!p) return fail(IBMC_E_OOM, "host allocation of %zu bytes failed", size);
+        }
+        blocks.push_back(Block{(char *)p, size, pinned});
         used = 0;
     }
-    *out = blocks.back().first + used;
+    *out = blocks.back().p + used;
     used += need;
     return IBMC_OK;
 }
 
-ibmc_status PinPool::reset() {
-    if (blocks.size() > 1) {
-        size_t total = 0;
-        for (auto &b : blocks) {
-            total += b.second;
-            HIP_OK(hipHostFree(b.first));
-        }
+void PinPool::reset() {
+    size_t total = 0;
+    for (auto &b : blocks) total += b.size;
+    if (blocks.size() > 1 || total > kPinKeep) {
+        for (auto &b : blocks) pin_free(b);
         blocks.clear();
         void *p = nullptr;
-        if (hipHostMalloc(&p, total, hipHostMallocDefault) == hipSuccess) blocks.emplace_back((char *)p, total);
-        else (void)hipGetLastError();   // taken piece by piece again
+        if (total > kPinKeep) total = 0;
+        if (total && hipHostMalloc(&p, total, hipHostMallocDefault) == hipSuccess) blocks.push_back(Block{(char *)p, total, true});
+        else if (total) (void)hipGetLastError();   // taken piece by piece again
     }
     used = 0;
-    return IBMC_OK;
 }
 
 ibmc_status resident_blocks(ibmc_ctx *ctx, const void *fn, size_t lds, int *occ) {

@@ -47,8 +47,8 @@ __device__ __forceinline__ void wave_unrank_subset(int64_t rank, int k, int n, i
 // A wave keeps its unit's weights of layers 2 .. L in registers, packed for
 // four-way dot products, over all of its candidates; bound by latency (one wave
 // per candidate, a few thousand candidates).  With a byte load and a wait per
-// weight 3,915 candidates of 30-40-30-6 took 116 us, now 49 us
-// (the weights in registers alone changed nothing; the unranking below did).
+// weight and unranking by lane loops 3,915 candidates of 30-40-30-6 took 116 us,
+// now 49 us (the weights alone changed nothing; the unranking above did).
 __global__ void __launch_bounds__(64) cov_cand_kernel(CovCandParams P) {
     __shared__ __attribute__((aligned(16))) int act[16];   // 64 activations, a byte each
     __shared__ unsigned long long mask[kCovSearchMaxWords];
