@@ -21,12 +21,11 @@ import numpy as np  # noqa: E402
 MI355X_INT8_PEAK_TOPS = 5000.0     # dense int8 MFMA, TOP/s
 MI355X_FP32_PEAK_TFLOPS = 157.3    # FP32 vector, TFLOP/s (half of it without packed FP32)
 MI355X_HBM_PEAK_GBS = 8000.0
-MI355X_SPEC_CLOCK_GHZ = 2.4
 HERE = os.path.dirname(os.path.abspath(__file__))
 # enumeration kernel sources whose hash keys the profile record
 TUNE_TABLE = os.path.join(HERE, "paper_1907_12933_amd", "tune_gfx950.json")
-KERNEL_SOURCES = ["paper_1907_12933_amd/csrc/enum_q8_impl.h", "paper_1907_12933_amd/csrc/enum_common.h",
-                  "paper_1907_12933_amd/csrc/ibmc_internal.h"]
+KERNEL_SOURCES = ["paper_1907_12933_amd/csrc/enum_fold_impl.h", "paper_1907_12933_amd/csrc/kernels_fold.h",
+                  "paper_1907_12933_amd/csrc/enum_fold.hip", "paper_1907_12933_amd/csrc/enum_common.h"]
 
 
 def kernel_source_sha():
@@ -39,12 +38,11 @@ def kernel_source_sha():
 
 
 def profile_record():
-    """The rocprofv3 figures of the enumeration kernel on this workload kept in
-    profiles/ (kernel-trace average duration of this benchmark's command, HBM
-    bytes per launch from FETCH_SIZE / WRITE_SIZE scaled by a plain copy's
-    counters, shader clock and matrix-pipe busy from the counter run), or None
-    once the kernel sources differ from the ones profiled."""
-    path = os.path.join(HERE, "profiles", "enum_q8_blob784.json")
+    """The rocprofv3 figures of the enumeration kernels of one step on this
+    workload kept in profiles/ (matrix instructions they execute, HBM bytes
+    from FETCH_SIZE / WRITE_SIZE scaled by a plain copy's counters, matrix-pipe
+    busy share), or None once the kernel sources differ from the ones profiled."""
+    path = os.path.join(HERE, "profiles", "enum_fold_blob784.json")
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
@@ -250,8 +248,8 @@ def batch_leg(ctx, ibmc, inputs):
                 counterexamples=int(sum(s["cex_total"] for s in sums)),
                 int8_roofline=dict(bound="mfma", achieved=round(ops / dev / 1e12, 2), peak=MI355X_INT8_PEAK_TOPS,
                                    unit="TOP/s", frac=round(ops / dev / 1e12 / MI355X_INT8_PEAK_TOPS, 4),
-                                   work="sum over properties of points x dense later-layer MACs x 2, "
-                                        "over the batch call's device time"),
+                                   work="sum over properties of points x the unfolded network's dense later-layer "
+                                        "MACs x 2, over the batch call's device time (folded networks execute a part)"),
                 fp32_properties=len(fp), fp32_points=fpts, fp32_seconds=round(tf, 4),
                 fp32_device_seconds=round(fdev, 4), fp32_points_per_s=fpts / tf,
                 fp32_near_ties=int(sum(s["near_ties_total"] for s in fs)),
@@ -536,31 +534,23 @@ def main():
     n_cex = sum(s["cex_total"] for s in sums)
     unsafe = sum(1 for s in sums if s["cex_total"] > 0)
 
-    # roofline of the enumeration kernel: algorithmic int8 MACs per point are
-    # the later layers' dense products (the first layer is the rank-k update);
-    # its duration is the average of HIP events around the enumeration launch
-    # alone, on the library's stream
+    # roofline of the enumeration: its duration is the average of HIP events
+    # around the enumeration launches alone, on the library's stream.  A folded
+    # network executes a part of the dense products only, so the fraction of the
+    # peak takes the matrix instructions counted on this workload; the rate that
+    # the unfolded network's dense products would need is given beside it
     macs_per_point = dense_macs(w.net.dims)
     k_avg = float(np.mean(ksec))
-    achieved_tops = 2.0 * macs_per_point * points / k_avg / 1e12
     prof = profile_record() if args.images == 64 else None
-    roof = dict(bound="mfma", achieved=round(achieved_tops, 2), peak=MI355X_INT8_PEAK_TOPS, unit="TOP/s",
-                frac=round(achieved_tops / MI355X_INT8_PEAK_TOPS, 4),
-                traffic=prof["hbm_bytes_per_launch"] if prof else None,
-                kernel="enum_q8", kernel_ms=round(k_avg * 1e3, 3),
-                ops_per_point=2 * macs_per_point, points_per_launch=points)
-    if prof:
-        # the same figures from the committed rocprofv3 summaries of this
-        # workload, and the ceiling at the shader clock measured there
-        clk = prof["shader_clock_ghz"]
-        roof.update(profile_kernel_ms=prof["kernel_trace_avg_ms"],
-                    profile_frac=round(2.0 * macs_per_point * points / (prof["kernel_trace_avg_ms"] * 1e-3) / 1e12
-                                       / MI355X_INT8_PEAK_TOPS, 4),
-                    measured_clock_ghz=clk, peak_at_measured_clock=round(MI355X_INT8_PEAK_TOPS * clk /
-                                                                         MI355X_SPEC_CLOCK_GHZ, 1),
-                    frac_at_measured_clock=round(achieved_tops / (MI355X_INT8_PEAK_TOPS * clk /
-                                                                  MI355X_SPEC_CLOCK_GHZ), 4),
-                    mfma_busy=prof.get("mfma_busy"))
+    ops = prof["mfma_ops_per_step"] if prof else None
+    achieved_tops = ops / k_avg / 1e12 if ops else None
+    roof = dict(bound="mfma", achieved=round(achieved_tops, 2) if ops else None, peak=MI355X_INT8_PEAK_TOPS, unit="TOP/s",
+                frac=round(achieved_tops / MI355X_INT8_PEAK_TOPS, 4) if ops else None,
+                traffic=prof["hbm_bytes_per_step"] if prof else None,
+                kernel="enum_fold", kernel_ms=round(k_avg * 1e3, 3), ops_executed=ops,
+                dense_equivalent=round(2.0 * macs_per_point * points / k_avg / 1e12, 2),
+                dense_ops_per_point=2 * macs_per_point, points_per_launch=points,
+                mfma_busy=prof.get("mfma_busy") if prof else None)
     out = {
         "metric": "perturbation points verified/sec + time-to-first-counterexample, plain vs learned",
         "value": value, "unit": "points/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
