@@ -22,13 +22,13 @@ constexpr int kF32SumBlock = 32;
 //   one point per lane: hidden widths padded to 16/32/64/128, at most two
 //     hidden layers, at most 16 classes; activations in registers (the second
 //     hidden layer in the wave's LDS), weights through the scalar cache;
-//   sixteen points per wave: every other shape (widths padded to multiples
-//     of 64, up to 512); lanes are neurons, the points' activations sit in
-//     the wave's LDS.
+//   sixteen points per workgroup: every other shape (widths padded to
+//     multiples of 64, up to 512); lanes are neurons, a wave per 64 of the widest
+//     layer, the points' activations sit in the workgroup's LDS.
 enum F32Kind : int32_t { F32_LANE = 0, F32_WIDE = 1 };
 
 constexpr int kF32LaneChunk = 64;   // points per chunk (one per lane)
-constexpr int kF32WideChunk = 16;   // points per chunk (per wave)
+constexpr int kF32WideChunk = 16;   // points per chunk (per workgroup)
 constexpr int kF32MaxWidth = 512;   // widest float layer the kernels accept
 
 // Padded layout of a float network for the enumeration kernels.

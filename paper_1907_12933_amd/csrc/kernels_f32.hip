@@ -156,10 +156,21 @@ hipError_t launch_replay_f32(const FNetDev &net, const uint8_t *clean, const int
 }
 
 // ---------------------------------------------------------------------------
-// sixteen points per wave (wide networks)
+// sixteen points per workgroup (wide networks)
 // ---------------------------------------------------------------------------
 
-// LDS of one wave: activations of 16 points in two buffers [16][wp], logits
+// A wave per 64 units of the widest layer, up to eight: the points'
+// activations fill the LDS (64 KB for 512 units), so that single waves left
+// two a compute unit, each waiting for its own weight loads (eight properties,
+// whole calls: 784-512-512-10, 20,384 points, 1,449 -> 707 us; 784-256-256-10,
+// 38,416 points, 568 -> 405 us; the clean labels of eight images 281 -> 79 us).
+static int wide_waves(const FNetDev &net) {
+    int h = 64;
+    for (int l = 1; l < net.L; ++l) h = std::max(h, net.HP[l]);
+    return std::min(8, h / 64);
+}
+
+// LDS of one workgroup: activations of 16 points in two buffers [16][wp], logits
 // [16][64], the segment's first-layer potentials before the last pixel [HP1].
 __host__ __device__ inline int wide_wp(const FNetDev &net) {
     int wp = 64;
@@ -170,16 +181,16 @@ static size_t wide_lds_bytes(const FNetDev &net) {
     return (size_t)(2 * 16 * wide_wp(net) + 16 * 64 + net.HP[1]) * 4;
 }
 
-// Layers >= 2 of 16 points (lanes = units, 64 at a time) from the
-// first-layer activations in act0 [16][wp]; logits to zs [16][64].
-__device__ void wide_upper(const FNetDev &net, float *act0, float *act1, float *zs, int wp, int lane) {
+// Layers >= 2 of 16 points (lanes = units, 64 at a time, spread over the waves)
+// from the first-layer activations in act0 [16][wp]; logits to zs [16][64].
+__device__ void wide_upper(const FNetDev &net, float *act0, float *act1, float *zs, int wp, int lane, int wave, int waves) {
     float *in = act0, *out = act1;
     for (int l = 2; l <= net.L; ++l) {
         const int nin = net.HP[l - 1], nout = net.HP[l];
         const float *W = net.WP[l];
         const float *B = net.bP[l];
         const bool last = l == net.L;
-        for (int jb = 0; jb < nout; jb += 64) {
+        for (int jb = 64 * wave; jb < nout; jb += 64 * waves) {
             const int j = jb + lane;
             float tot[16];
             const float bj = B[j];
@@ -213,7 +224,7 @@ __device__ void wide_upper(const FNetDev &net, float *act0, float *act1, float *
                 for (int t = 0; t < 16; ++t) zs[t * 64 + j] = tot[t];
             }
         }
-        wave_lds_sync();
+        __syncthreads();
         float *tmp = in;
         in = out;
         out = tmp;
@@ -233,23 +244,33 @@ __device__ __forceinline__ void wide_decide(const float *zs, int nc, int lane, i
     margin = top - second;
 }
 
-__global__ void __launch_bounds__(64) enum_f32_wide_kernel(FEnumParams P) {
+__global__ void __launch_bounds__(512) enum_f32_wide_kernel(FEnumParams P) {
     constexpr int CH = kF32WideChunk;
+    __shared__ int64_t ticket[2];   // wave 0's, for all
     extern __shared__ __attribute__((aligned(16))) float wlds[];
     const FNetDev &net = P.net;
     const int wp = wide_wp(net), hp1 = net.HP[1], nc = net.dims[net.L];
     float *act0 = wlds, *act1 = wlds + 16 * wp, *zs = wlds + 32 * wp, *base = wlds + 32 * wp + 16 * 64;
-    const int lane = __lane_id();
+    const int lane = __lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
     Cursor c;
     int64_t cur = 0, end = 0;
     bool seg_new = true;
     int prop_seen = -1, label0 = 0;
-    int q = f32_first_slice(), tries = 0, polls = 0;
+    int q = blockIdx.x % kF32Queues, tries = 0, polls = 0;
     while (true) {
         if (cur >= end) {
-            const int64_t start = f32_ticket(P, q, tries, end, polls);
-            if (start < 0) break;
-            cur = start;
+            if (wave == 0) {
+                int64_t last = 0;
+                const int64_t first = f32_ticket(P, q, tries, last, polls);
+                if (lane == 0) {
+                    ticket[0] = first;
+                    ticket[1] = last;
+                }
+            }
+            __syncthreads();
+            cur = (int64_t)wave_uniform((unsigned long long)ticket[0]);
+            end = (int64_t)wave_uniform((unsigned long long)ticket[1]);
+            if (cur < 0) break;
             cursor_decode<CH, FEnumParams>(c, P, cur);
             seg_new = true;
         }
@@ -266,12 +287,12 @@ __global__ void __launch_bounds__(64) enum_f32_wide_kernel(FEnumParams P) {
             float ee[kMaxK];
             segment_prefix(c, pp, ee);
             const float *u0 = P.u0f + (int64_t)c.prop * P.u0_stride;
-            for (int jb = 0; jb < hp1; jb += 64)
+            for (int jb = 64 * wave; jb < hp1; jb += 64 * waves)
                 base[jb + lane] = prefix_potential_rt(net, hp1, u0, c.k - 1, pp, ee, jb + lane);
             seg_new = false;
         }
         // first layer: each point's last pixel on the segment's potentials
-        for (int jb = 0; jb < hp1; jb += 64) {
+        for (int jb = 64 * wave; jb < hp1; jb += 64 * waves) {
             const int j = jb + lane;
             const float vb = base[j];
 #pragma unroll 4
@@ -281,29 +302,31 @@ __global__ void __launch_bounds__(64) enum_f32_wide_kernel(FEnumParams P) {
                 act0[t * wp + j] = sigmoid_f32(fmaf(et, net.W1P[(int64_t)pt * hp1 + j], vb));
             }
         }
-        wave_lds_sync();
-        wide_upper(net, act0, act1, zs, wp, lane);
-        int best;
-        float top, margin;
-        wide_decide(zs, nc, lane, best, top, margin);
-        wave_lds_sync();   // the logits are read before the next chunk overwrites them
-        const bool near = valid && margin <= P.tie_rel * fmaxf(1.0f, fabsf(top));
-        const bool viol = valid && best != label0;
-        emit_f32(P, c, viol, near, p, i, best);
+        __syncthreads();
+        wide_upper(net, act0, act1, zs, wp, lane, wave, waves);
+        if (wave == 0) {
+            // (the next logits are two barriers away)
+            int best;
+            float top, margin;
+            wide_decide(zs, nc, lane, best, top, margin);
+            const bool near = valid && margin <= P.tie_rel * fmaxf(1.0f, fabsf(top));
+            const bool viol = valid && best != label0;
+            emit_f32(P, c, viol, near, p, i, best);
+        }
         cur++;
         if (cur < end) seg_new = cursor_next<CH, FEnumParams>(c, P);
     }
 }
 
-// Listed points, sixteen per wave, through the same arithmetic: each point's
+// Listed points, sixteen per workgroup, through the same arithmetic: each point's
 // first-layer potentials start from u0 and take its prefix pixels in
 // ascending order, then its last pixel.
-__global__ void __launch_bounds__(64) eval_f32_wide_kernel(F32EvalParams E) {
+__global__ void __launch_bounds__(512) eval_f32_wide_kernel(F32EvalParams E) {
     extern __shared__ __attribute__((aligned(16))) float wlds[];
     const FNetDev &net = E.net;
     const int wp = wide_wp(net), hp1 = net.HP[1], nc = net.dims[net.L];
     float *act0 = wlds, *act1 = wlds + 16 * wp, *zs = wlds + 32 * wp;
-    const int lane = __lane_id();
+    const int lane = __lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
     const int64_t t0 = (int64_t)blockIdx.x * 16 + (lane & 15);
     const bool ok = lane < 16 && t0 < E.n;
     const int64_t tt = t0 < E.n ? t0 : 0;
@@ -325,7 +348,7 @@ __global__ void __launch_bounds__(64) eval_f32_wide_kernel(F32EvalParams E) {
         if (j < np) { pp[j] = pix[j]; ee[j] = eff_delta(pr.image[pix[j]], pr.deltas[dig[j]]); }
         if (k > 0 && j == k - 1) { p = pix[j]; e = eff_delta(pr.image[pix[j]], pr.deltas[dig[j]]); }
     }
-    for (int jb = 0; jb < hp1; jb += 64) {
+    for (int jb = 64 * wave; jb < hp1; jb += 64 * waves) {
         const int j = jb + lane;
         for (int t = 0; t < 16; ++t) {
             const int pt = __builtin_amdgcn_readlane(prop, t);
@@ -343,8 +366,9 @@ __global__ void __launch_bounds__(64) eval_f32_wide_kernel(F32EvalParams E) {
             act0[t * wp + j] = sigmoid_f32(fmaf(et, net.W1P[(int64_t)ptl * hp1 + j], v));
         }
     }
-    wave_lds_sync();
-    wide_upper(net, act0, act1, zs, wp, lane);
+    __syncthreads();
+    wide_upper(net, act0, act1, zs, wp, lane, wave, waves);
+    if (wave != 0) return;
     int best;
     float top, margin;
     wide_decide(zs, nc, lane, best, top, margin);
@@ -416,7 +440,7 @@ int f32_enum_grid(const FNetDev &net, int n_cu, bool table) {
             return 0;
         return std::max(occ, 1) * n_cu * kLaneWaves;
     }
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, enum_f32_wide_kernel, 64, wide_lds_bytes(net)) !=
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, enum_f32_wide_kernel, 64 * wide_waves(net), wide_lds_bytes(net)) !=
         hipSuccess)
         return 0;
     return std::max(occ, 1) * n_cu;
@@ -430,7 +454,7 @@ hipError_t launch_enum_f32(int grid_waves, const FEnumParams &P, hipStream_t s) 
         void *args[] = {&a};
         return hipLaunchKernel(v->enum_fn[P.lut ? 1 : 0], dim3((grid_waves + kLaneWaves - 1) / kLaneWaves), dim3(256), args, 0, s);
     }
-    hipLaunchKernelGGL(enum_f32_wide_kernel, dim3(grid_waves), dim3(64), wide_lds_bytes(P.net), s, P);
+    hipLaunchKernelGGL(enum_f32_wide_kernel, dim3(grid_waves), dim3(64 * wide_waves(P.net)), wide_lds_bytes(P.net), s, P);
     return hipGetLastError();
 }
 
@@ -443,7 +467,7 @@ hipError_t launch_eval_f32(const F32EvalParams &E, hipStream_t s) {
         void *args[] = {&a};
         return hipLaunchKernel(v->eval_fn[E.lut ? 1 : 0], dim3((unsigned)((E.n + 255) / 256)), dim3(256), args, 0, s);
     }
-    hipLaunchKernelGGL(eval_f32_wide_kernel, dim3((unsigned)((E.n + 15) / 16)), dim3(64), wide_lds_bytes(E.net), s, E);
+    hipLaunchKernelGGL(eval_f32_wide_kernel, dim3((unsigned)((E.n + 15) / 16)), dim3(64 * wide_waves(E.net)), wide_lds_bytes(E.net), s, E);
     return hipGetLastError();
 }
 
