@@ -1,6 +1,6 @@
 // Float-network (sigmoid variant) kernels: plain forward and replay (the
 // dense reference path, device expf), the clean pass of the enumeration, the
-// sixteen-points-per-wave enumeration for wide networks, evaluation of
+// sixteen-points-per-workgroup enumeration for wide networks, evaluation of
 // listed points with the enumeration arithmetic, and the launchers that pick
 // a kernel family per network.
 #include "kernels_f32.h"
