@@ -117,8 +117,11 @@ __device__ __forceinline__ void lane_decide(const int (&in)[NI / 4], const LaneW
 // ball, whether the prefix stays in [0, 255] and its squared length, and skips
 // the segment's chunks if it doesn't); per chunk it tallies counterexamples,
 // exact ties and visited points of the level.
+// Three waves a SIMD: four spill a few registers, and the scratch memory alone
+// costs a short call 50 us (16-20-9, one image, 300,000 positions: 320 us a call
+// against 256).
 template <int H1, int H2>
-__global__ void __launch_bounds__(256, 4) enum_lane_kernel(LaneParams P) {
+__global__ void __launch_bounds__(256, 3) enum_lane_kernel(LaneParams P) {
     constexpr int CH = kLaneChunk;
     constexpr int HL = H2 > 0 ? H2 : H1;
     __shared__ __attribute__((aligned(16))) int32_t bases[kLaneWaves][H1];

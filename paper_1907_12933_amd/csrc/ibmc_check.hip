@@ -134,6 +134,15 @@ static ibmc_status send_inputs(ibmc_ctx *ctx, BatchState &B) {
 }
 
 // Digits per pixel side of the L2-ball domain: min(floor(sqrt(r2)), 255).
+// Chunks per ticket of a lane kernel whose waves have n chunks each.  A ticket
+// costs a search of the job tables, about two chunks' time, and the last one
+// leaves half a ticket of waiting on average: n + 2 n / b + b / 2 is least at
+// 2 sqrt(n).  (n / 8, at most 16, before: ten glyphs' L2 balls 1.8 ms where 64
+// take 1.5, and one chunk a ticket below 16 chunks per wave.)
+static int32_t lane_batch(int64_t n) {
+    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(64, n), (int64_t)(2.0 * std::sqrt((double)n))));
+}
+
 static int ball_rd(int64_t r2) {
     int64_t r = 0;
     while (r < 255 && (r + 1) * (r + 1) <= r2) ++r;
@@ -916,7 +925,7 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
             P.total_chunks = pl.total;
             P.slice = std::max<int64_t>(1, (pl.total + kF32Queues - 1) / kF32Queues);
             const int64_t waves_per_slice = std::max<int64_t>(1, (int64_t)pl.grid * 4 / kF32Queues);
-            P.batch = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, P.slice / (waves_per_slice * 8)));
+            P.batch = lane_batch(P.slice / waves_per_slice);
             P.props = dprops;
             P.u0 = ctx->u0.as<int32_t>();
             P.u0_stride = (int32_t)max_h1;
@@ -968,12 +977,11 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
             P.n_jobs = (int32_t)pl.n_jobs;
             P.total_chunks = pl.total;
             // slices of the chunk range, each with its own queue counter;
-            // tickets of up to 64 chunks, about 8 per wave of a slice (each
-            // costs a search of the job tables: ten glyphs' L2 balls 1.8 -> 1.5 ms
-            // against at most 16, 35-16-5 77 -> 84 billion points per second)
+            // (wide networks' chunks take long: about 8 tickets per wave, of up to 16)
             P.slice = std::max<int64_t>(1, (pl.total + kF32Queues - 1) / kF32Queues);
             const int64_t waves_per_slice = std::max<int64_t>(1, pl.grid / kF32Queues);
-            P.batch = (int32_t)std::max<int64_t>(1, std::min<int64_t>(64, P.slice / (waves_per_slice * 8)));
+            P.batch = P.net.kind == F32_LANE ? lane_batch(P.slice / waves_per_slice)
+                                             : (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, P.slice / (waves_per_slice * 8)));
             P.props = dprops;
             P.u0f = ctx->u0.as<float>();
             P.u0_stride = (int32_t)max_h1;
