@@ -384,7 +384,8 @@ static bool fold_scale(const ibmc_mlp *net, int maxe, int &f, int &halvings, int
 // the counts back, gathers the reduced networks, and moves the folded
 // properties from the plans into buckets.  A property is folded when its
 // reduced network is clearly smaller than the kernel instance it would run
-// on; the others stay, with their clean pass done.  Nothing is folded for a
+// on and its output differences fit two bytes; the others stay, with their
+// clean pass done.  Nothing is folded for a
 // resumable call (its chunk numbers are part of the interface), the literal,
 // the L2 ball, a forced variant, the int32 testing aid, or when buffers come
 // from the fixed scratch array.
@@ -498,7 +499,7 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
         const ibmc_mlp *net = net_plan[c.net]->net;
         const QNetDev &q = net->qd;
         const int live1 = live[4 * i], live2 = live[4 * i + 1] & 0xffff, two = live[4 * i + 2], L = net->L;
-        if (c.points == 0 || live1 > kFoldMaxWidth) continue;
+        if (c.points == 0 || live1 > kFoldMaxWidth || two > 1) continue;
         int kw = 0;
         for (int w : kFoldWidths)
             if (kw < live1 || kw == 0) kw = w;

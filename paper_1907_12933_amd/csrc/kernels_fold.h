@@ -29,8 +29,8 @@ struct FoldProp {
     int32_t dlo, dhi;      // smallest and largest delta, widened to contain 0
     int32_t joint;         // layers 1 and 2 hold no weight of -128 (the joint bound's absolute values fit int8)
     int32_t *ws;           // see FoldWs
-    int32_t *counts;       // [4]: live units of layer 1; of layer 2 | uncapped pairs of tiles << 16; output differences
-                           // that need two bytes; clean label
+    int32_t *counts;       // [4]: live units of layer 1; of layer 2 | uncapped pairs of tiles << 16; whether output
+                           // differences need two bytes (1) or don't fit two (2); clean label
 };
 
 // Layout of a property's scan results (words).

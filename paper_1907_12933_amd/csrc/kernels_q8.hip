@@ -280,9 +280,10 @@ __device__ int fold_compact(bool flag, int value, int32_t *list, int *cnt) {
 }
 
 // Output layer of a folded property, a wave per row: bias with the constant
-// inputs, and the live inputs' weights times their offsets; then whether a
-// weight difference to the label's row leaves int8 on a live input.  iv(i):
-// input i's interval as lowest | highest << 8; off(i): its offset.
+// inputs, and the live inputs' weights times their offsets; then into `two`
+// (0 before) whether a weight difference to the label's row leaves int8 on a
+// live input (1) or is 127 - (-128) = 255, which no two int8 add up to (2).
+// iv(i): input i's interval as lowest | highest << 8; off(i): its offset.
 template <class IV, class OFF>
 __device__ void fold_output(const QNetDev &net, int lab, int32_t *bo, int32_t *rso, int *two, IV iv, OFF off) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
@@ -296,13 +297,13 @@ __device__ void fold_output(const QNetDev &net, int lab, int32_t *bo, int32_t *r
             const bool fixed = a == ((v >> 8) & 0xff);
             cs += fixed ? c * a : 0;
             sum += fixed ? 0 : c * off(i);
-            wide |= !fixed && (d < -128 || d > 127);
+            wide |= fixed ? 0 : (d < -128 || d > 127) | (d > 254) << 1;
         }
         for (int d = 32; d > 0; d >>= 1) {
             cs += __shfl_xor(cs, d);
             sum += __shfl_xor(sum, d);
         }
-        if (__ballot(wide) && lane == 0) *two = 1;
+        if (wide) atomicOr(two, wide);
         if (lane == 0) {
             bo[r] = net.bd[L][r] + cs;
             rso[r] = sum;
