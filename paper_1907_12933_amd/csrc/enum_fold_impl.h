@@ -2,6 +2,7 @@
 #pragma once
 
 #include "enum_q8_impl.h"
+#include "fold_search.h"
 #include "kernels_fold.h"
 
 namespace ibmc {
@@ -90,20 +91,13 @@ __device__ __forceinline__ int rows_max(int x) {
     return max(b.lo, b.hi);
 }
 
-// Last job whose first chunk is at or before `chunk`: two rounds of 64-way
-// comparison instead of a serial search (n_jobs <= 4096).
+// Last job whose first chunk is at or before `chunk` (job 0 starts at chunk 0):
+// 64-way comparison instead of a serial search.
 __device__ __forceinline__ int fold_find_job(const EnumJob *jobs, int n_jobs, int64_t chunk, int lane) {
-    const int step = (n_jobs + 63) >> 6;
-    int i = lane * step;
-    bool le = i < n_jobs && gld(&jobs[min(i, n_jobs - 1)].chunk_begin) <= chunk;
-    const int blk = __popcll(__ballot(le)) - 1;          // job 0 starts at chunk 0
-    int lo = blk * step;
-    if (step > 1) {
-        i = lo + lane;
-        le = lane < step && i < n_jobs && gld(&jobs[min(i, n_jobs - 1)].chunk_begin) <= chunk;
-        lo += __popcll(__ballot(le)) - 1;
-    }
-    return wave_uniform(lo);
+    return wave_uniform(fold_search(n_jobs, [&](int first, int step, int n) __attribute__((always_inline)) {
+        const int i = lane * step;
+        return __popcll(__ballot(i < n && gld(&jobs[first + min(i, n - 1)].chunk_begin) <= chunk));
+    }));
 }
 
 // LDS of one wave.

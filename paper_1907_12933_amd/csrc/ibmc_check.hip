@@ -335,10 +335,6 @@ struct FoldBucket {
     std::vector<Part> parts;
 };
 
-// Points of one job of a folded level at most: an aborted check keeps whole
-// jobs (tens of milliseconds each).
-constexpr int64_t kFoldJobPoints = (int64_t)1 << 31;
-
 // What folding saves is worth its extra work (scan, one read-back, gather) from
 // this many points of a call on, a point of a three-layer network (whose scan
 // has a second kernel) counting kFoldPoint3.  Measured as whole calls with and
@@ -401,7 +397,7 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
     std::vector<Cand> cands;
     std::vector<QNetDev> nets;
     std::vector<NetPlan *> net_plan;
-    size_t ws_ints = 0, n_jobs = 0;
+    size_t ws_ints = 0, n_levels = 0;
     double est = 0.0;
     for (NetPlan &pl : plans) {
         const ibmc_mlp *net = pl.net;
@@ -416,7 +412,7 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
             for (int li : level_sel[pid]) {
                 const int k = B.level_k[pid][li];
                 c.k = std::max(c.k, k);
-                ++n_jobs;
+                ++n_levels;
                 if (k > 0) c.points += binom_small(net->dims[0], k) * ipow64(props[pid].n_deltas, k);
             }
             for (int j = 0; j < props[pid].n_deltas && !B.hprops[pid].ball; ++j)
@@ -432,8 +428,7 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
         nets.push_back(net->qd);
         net_plan.push_back(&pl);
     }
-    // (kFoldMaxJobs: the kernel's job search)
-    if (cands.empty() || est < kFoldMinPoints || ws_ints * 4 > kFoldMaxBytes || n_jobs > kFoldMaxJobs) return IBMC_OK;
+    if (cands.empty() || est < kFoldMinPoints || ws_ints * 4 > kFoldMaxBytes || n_levels > kFoldMaxLevels) return IBMC_OK;
 
     // scan: [networks][properties][block map] in, counts and lists out
     const size_t nc = cands.size();
@@ -806,7 +801,7 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
                         continue;
                     }
                     const int64_t T = 4 * (int64_t)b.batch;
-                    const int64_t cut = std::max(kFoldJobPoints / ((int64_t)CH * W), ch / 256);
+                    const int64_t cut = std::max(ctx->fold_job_points / ((int64_t)CH * W), ch / 256);
                     const size_t qo = k >= 2 ? qcum_all.size() : (size_t)-1;
                     if (k >= 2) qcum_all.insert(qcum_all.end(), qc.begin(), qc.end());
                     int64_t from = 0;

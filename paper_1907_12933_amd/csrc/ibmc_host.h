@@ -135,6 +135,9 @@ struct ibmc_ctx {
     std::string graph_sig;
     int64_t graph_reuses = 0;
     bool force_int32_layer1 = false;   // testing aid: take the general first-layer path
+    // points of one job of a folded level at most: an aborted check keeps whole
+    // jobs (tens of milliseconds each)
+    int64_t fold_job_points = (int64_t)1 << 31;
     double last_kernel_seconds = 0.0;
     int last_kernel_launches = 0;
     ~ibmc_ctx();

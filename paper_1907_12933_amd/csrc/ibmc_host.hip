@@ -175,6 +175,8 @@ extern "C" ibmc_status ibmc_ctx_create(int32_t device, void *hip_stream, ibmc_ct
     // testing aid: IBMC_FIRST_LAYER=int32 forces the general (int32) first-layer path
     const char *fl = getenv("IBMC_FIRST_LAYER");
     c->force_int32_layer1 = fl && std::string(fl) == "int32";
+    // testing aid: IBMC_FOLD_JOB_POINTS cuts the folded levels into smaller jobs
+    if (const char *fj = getenv("IBMC_FOLD_JOB_POINTS")) c->fold_job_points = std::max(1ll, std::atoll(fj));
     if (hip_stream) {
         c->stream = reinterpret_cast<hipStream_t>(hip_stream);
         c->own_stream = false;

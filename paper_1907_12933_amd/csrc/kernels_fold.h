@@ -17,7 +17,7 @@ __host__ __device__ constexpr int fold_blocks(int kw) { return kw <= 64 ? 1 : kw
 __host__ __device__ constexpr int fold_units_per_block(int kw) { return kw / (4 * fold_blocks(kw)); }
 constexpr int kFoldMaxWidth = 256;
 constexpr int kFoldGroup = 8;                       // segments per group at most
-constexpr int kFoldMaxJobs = 4096;                  // jobs of one launch at most (64 x 64 search)
+constexpr int kFoldMaxLevels = 4096;                // levels of all folded properties of a call at most
 constexpr const char *kFoldVariantName = "fold";    // forces folding whatever the workload's size
 constexpr int kFoldMaxStage = 96 * 1024;            // bytes of staged weights per workgroup at most
 
