@@ -1102,6 +1102,7 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
             put(&pl.packed, sizeof(pl.packed));
             put(&pl.vb_lo, sizeof(pl.vb_lo));
             put(&pl.vb_hi, sizeof(pl.vb_hi));
+            put(&pl.scanned, sizeof(pl.scanned));   // whether its clean pass is in the graph
             put(&nid, sizeof(nid));
         }
         const void *bufs[] = {d_jobs, ctr, ctx->recs.p, ctx->ties.p, ctx->u0.p, d_u0_index,
