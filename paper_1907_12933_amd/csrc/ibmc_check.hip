@@ -1090,7 +1090,7 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         auto put = [&sig](const void *p, size_t n) { sig.append(reinterpret_cast<const char *>(p), n); };
         for (const NetPlan &pl : plans) {
             const size_t nid = pl.ids.size();
-            put(&pl.net, sizeof(pl.net));
+            put(&pl.net->id, sizeof(pl.net->id));   // its layout is in the captured parameters
             put(&pl.lane, sizeof(pl.lane));
             put(&pl.v, sizeof(pl.v));
             put(&pl.total, sizeof(pl.total));

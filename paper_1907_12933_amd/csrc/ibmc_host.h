@@ -144,6 +144,7 @@ struct ibmc_ctx {
 };
 
 struct ibmc_mlp {
+    const uint64_t id = next_id();     // of this load, never used again (an address may be)
     ibmc_ctx *ctx = nullptr;
     int device = -1;
     int act = 0;
@@ -163,6 +164,7 @@ struct ibmc_mlp {
     bool fold_ok = false;              // integer nets whose properties may be folded
     bool fold_joint = false;           // their first two layers hold no weight of -128
     std::string forced_variant;
+    static uint64_t next_id();
     ~ibmc_mlp();
 };
 

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cstdlib>
 #include <chrono>
 #include <cmath>
@@ -250,6 +251,11 @@ extern "C" ibmc_status ibmc_last_kernel_time(ibmc_ctx *ctx, double *seconds, int
 // ---------------------------------------------------------------------------
 // networks
 // ---------------------------------------------------------------------------
+
+uint64_t ibmc_mlp::next_id() {
+    static std::atomic<uint64_t> last{0};
+    return ++last;
+}
 
 ibmc_mlp::~ibmc_mlp() {
     // the device is kept here, not read from the context, which may be gone
