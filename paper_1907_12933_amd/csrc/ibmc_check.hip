@@ -1782,6 +1782,7 @@ ibmc_status ordered_search(ibmc_ctx *ctx, const ibmc_mlp *net, const ibmc_propos
     if (o->property != IBMC_PROPERTY_LABEL || o->sigmoid != IBMC_SIGMOID_EXP)
         return fail(IBMC_E_UNIMPL, "the ordered search checks the label property with the exponential sigmoid");
     HIP_OK(hipSetDevice(ctx->device));
+    ctx->pin.reset();
     hipStream_t s = ctx->stream;
     const int n = net->dims[0];
     const int64_t N1 = (int64_t)n * m;
