@@ -218,12 +218,12 @@ static ibmc_status fetch_sorted(ibmc_ctx *ctx, const DevRec *drecs, int64_t n, i
         // one workgroup sorts and unpacks; the records and their number come
         // back in one copy
         const int64_t m = std::min(n, keep);
-        const size_t o_rec = 256;
-        IBMC_TRY(ctx->recout.reserve(o_rec + (direct_dev ? 0 : (size_t)m * sizeof(CexRec))));
-        char *buf = ctx->recout.as<char>();
+        const size_t o_rec = 256, bytes = o_rec + (direct_dev ? 0 : (size_t)m * sizeof(CexRec));
+        // (the radix sort's space, which holds more than that for these slots)
+        IBMC_TRY(ctx->sortbuf.reserve(sort_scratch_bytes(n)));
+        char *buf = ctx->sortbuf.as<char>();
         CexRec *dout = direct_dev ? direct : reinterpret_cast<CexRec *>(buf + o_rec);
         HIP_OK(launch_sort_small(drecs, n, m, max_prop, max_k, max_rank, dout, reinterpret_cast<int64_t *>(buf), s));
-        const size_t bytes = o_rec + (direct_dev ? 0 : (size_t)m * sizeof(CexRec));
         void *hp = nullptr;
         IBMC_TRY(ctx->pin.take(bytes, &hp));
         HIP_OK(hipMemcpyAsync(hp, buf, bytes, hipMemcpyDeviceToHost, s));

@@ -76,22 +76,25 @@ struct DevBuf {
 
 // Pinned host memory of one call's uploads and read-backs: pieces are taken in
 // order and stay valid until the next call's reset (a call returns with its
-// stream idle).  Copies from and to it queue without a wait on the host.
+// stream idle).  Copies from and to it queue without a wait on the host.  The
+// blocks stay until the context goes, kPinKeep bytes at most.  Beyond that, where
+// nothing can be pinned, and beyond the blocks at hand while an arena is installed
+// (the allocation-free entry point) pageable memory stands in, more slowly.
 struct PinPool {
-    static constexpr size_t kPinKeep = (size_t)64 << 20;   // more is given back before the next call
+    static constexpr size_t kPinFirst = (size_t)256 << 10;  // the block a context starts with
+    static constexpr size_t kPinKeep = (size_t)64 << 20;
     struct Block {
         char *p;
-        size_t size;
+        size_t size, used;
         bool pinned;
     };
-    std::vector<Block> blocks;                       // the last one is being carved
-    size_t used = 0;
+    std::vector<Block> blocks;
     PinPool() = default;
     PinPool(const PinPool &) = delete;
     PinPool &operator=(const PinPool &) = delete;
     ~PinPool();
     ibmc_status take(size_t n, void **out);          // 256-byte aligned
-    void reset();                                    // several blocks become one of their total size
+    void reset();                                    // every piece is given back, and the pageable memory
 };
 
 }  // namespace ibmc

@@ -103,37 +103,39 @@ PinPool::~PinPool() {
 
 ibmc_status PinPool::take(size_t n, void **out) {
     const size_t need = (std::max<size_t>(n, 1) + 255) & ~(size_t)255;
-    if (blocks.empty() || blocks.back().size - used < need) {
-        const size_t size = std::max<size_t>(need, (size_t)256 << 10);
-        void *p = nullptr;
-        bool pinned = true;
-        if (hipHostMalloc(&p, size, hipHostMallocDefault) != hipSuccess) {
-            // pageable memory does, more slowly
-            (void)hipGetLastError();
-            pinned = false;
-            p = std::aligned_alloc(256, (size + 255) & ~(size_t)255);
-            if (!p) return fail(IBMC_E_OOM, "host allocation of %zu bytes failed", size);
+    size_t total = 0;
+    for (Block &b : blocks) {
+        if (b.size - b.used >= need) {
+            *out = b.p + b.used;
+            b.used += need;
+            return IBMC_OK;
         }
-        blocks.push_back(Block{(char *)p, size, pinned});
-        used = 0;
+        total += b.pinned ? b.size : 0;
     }
-    *out = blocks.back().p + used;
-    used += need;
+    // as much again as is there already, so that there are few blocks
+    size_t size = std::max({need, kPinFirst, total});
+    if (total + size > kPinKeep) size = std::max(need, kPinFirst);
+    void *p = nullptr;
+    bool pinned = !thread_arena() && total + size <= kPinKeep;
+    if (pinned && hipHostMalloc(&p, size, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        pinned = false;
+    }
+    if (!pinned) {
+        size = need;
+        p = std::aligned_alloc(256, size);
+        if (!p) return fail(IBMC_E_OOM, "host allocation of %zu bytes failed", size);
+    }
+    blocks.push_back(Block{(char *)p, size, need, pinned});
+    *out = p;
     return IBMC_OK;
 }
 
 void PinPool::reset() {
-    size_t total = 0;
-    for (auto &b : blocks) total += b.size;
-    if (blocks.size() > 1 || total > kPinKeep) {
-        for (auto &b : blocks) pin_free(b);
-        blocks.clear();
-        void *p = nullptr;
-        if (total > kPinKeep) total = 0;
-        if (total && hipHostMalloc(&p, total, hipHostMallocDefault) == hipSuccess) blocks.push_back(Block{(char *)p, total, true});
-        else if (total) (void)hipGetLastError();   // taken piece by piece again
-    }
-    used = 0;
+    const auto end = std::stable_partition(blocks.begin(), blocks.end(), [](const Block &b) { return b.pinned; });
+    std::for_each(end, blocks.end(), pin_free);
+    blocks.erase(end, blocks.end());
+    for (Block &b : blocks) b.used = 0;
 }
 
 ibmc_status resident_blocks(ibmc_ctx *ctx, const void *fn, size_t lds, int *occ) {
@@ -201,6 +203,8 @@ extern "C" ibmc_status ibmc_ctx_create(int32_t device, void *hip_stream, ibmc_ct
     HIP_OK(hipHostGetDevicePointer(&dm, hm, 0));
     c->flags_dev = reinterpret_cast<int32_t *>(dm);
     IBMC_TRY(noalloc_setup(device));
+    void *first = nullptr;
+    IBMC_TRY(c->pin.take(1, &first));   // the first block, which the allocation-free entry point relies on
     *out = c.release();
     return IBMC_OK;
 }

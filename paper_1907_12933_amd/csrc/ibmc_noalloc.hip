@@ -2,7 +2,8 @@
 // allocate device memory (code under HIP graph capture, tight serving
 // loops).  Every device buffer of the call is carved, in order, from one
 // fixed array that the library holds per device for the life of the
-// process; nothing is allocated or freed.
+// process, its host staging from the context's pinned block or the heap;
+// no device or pinned memory is allocated or freed.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -41,10 +42,15 @@ ibmc_status noalloc_setup(int device) {
 
 static size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Upper bound of the bytes one call carves (every buffer the check driver
-// reserves for a single property, each 256-byte aligned).
-static ibmc_status scratch_need(ibmc_ctx *ctx, const ibmc_mlp *net, int32_t n_deltas, const ibmc_check_opts *o,
-                                size_t *need) {
+// What one call carves at most.  need: the bytes that decide whether it is
+// accepted, a bound of all of it.  The others: the buffers whose size may
+// change from one level to the next (stop_at_first), each reserved once at its
+// largest, before any device work.
+struct ScratchNeed {
+    size_t need = 0, plan = 0, recs = 0, sort = 0, out = 0;
+};
+
+static ibmc_status scratch_need(ibmc_ctx *ctx, const ibmc_mlp *net, const ibmc_check_opts *o, ScratchNeed &N) {
     const int n = net->dims[0];
     int levels = 0;
     for (int k = o->k_min; k <= o->k_max; k += o->k_step) ++levels;
@@ -63,21 +69,25 @@ static ibmc_status scratch_need(ibmc_ctx *ctx, const ibmc_mlp *net, int32_t n_de
     } else {
         h1 = std::max<int64_t>(h1, net->dims[1]);
     }
-    (void)n_deltas;
-    size_t b = 0;
-    b += al256((size_t)((n + 15) / 16 * 16));                       // image
-    b += al256(sizeof(PropDev));                                     // property
-    b += al256((size_t)(8 + 1 + 3 * levels + kQueueStride + kF32Queues * kQueueStride) * 8);  // counters, queues
-    b += al256((size_t)std::max<int64_t>(tcap, 1) * sizeof(DevRec)); // near-tie slots
-    b += al256((size_t)h1 * 4) + 2 * al256(4);                       // u0, u0 index, property ids
-    b += al256((size_t)std::max(levels, 1) * n * 8);                 // prefix tables
-    b += al256((size_t)std::max(levels, 1) * sizeof(EnumJob));       // jobs
-    b += al256((size_t)std::max<int64_t>(rec_slots, 1) * sizeof(DevRec));
-    b += al256(sort_scratch_bytes(rec_slots)) + al256(sort_scratch_bytes(tcap));
-    if (!o->records_on_device)
-        b += al256((size_t)std::max<int64_t>(cap, 1) * sizeof(CexRec)) + al256((size_t)std::max<int64_t>(tcap, 1) * sizeof(CexRec));
-    b += 2 * 512;                                                    // record counts of short lists
-    *need = b;
+    // counters and queues | jobs | prefix tables | property id | u0 index
+    const size_t counters = al256((size_t)(8 + 1 + 3 * levels + kQueueStride + kF32Queues * kQueueStride) * 8);
+    const size_t tables = al256((size_t)std::max(levels, 1) * n * 8) + 2 * al256(4);
+    N.plan = counters + al256((size_t)std::max(levels, 1) * sizeof(EnumJob)) + tables;
+    N.recs = al256((size_t)std::max<int64_t>(rec_slots, 1) * sizeof(DevRec));
+    // the two lists are sorted one after the other in one space and go out
+    // through one buffer, but count with one of their own each, as they always
+    // have: that leaves room for what jobs have grown by and the table sigmoid
+    const size_t sort1 = al256(sort_scratch_bytes(rec_slots)), sort2 = al256(sort_scratch_bytes(tcap));
+    N.sort = std::max(sort1, sort2);
+    N.need = al256((size_t)((n + 15) / 16 * 16)) + al256(sizeof(PropDev)) + al256((size_t)h1 * 4) + counters + tables +
+             al256((size_t)std::max(levels, 1) * (sizeof(EnumJob) - sizeof(EnumJob::r0))) +
+             al256((size_t)std::max<int64_t>(tcap, 1) * sizeof(DevRec)) + N.recs + sort1 + sort2;
+    if (!o->records_on_device) {
+        const size_t out1 = al256((size_t)std::max<int64_t>(cap, 1) * sizeof(CexRec));
+        const size_t out2 = al256((size_t)std::max<int64_t>(tcap, 1) * sizeof(CexRec));
+        N.out = std::max(out1, out2);
+        N.need += out1 + out2;
+    }
     return IBMC_OK;
 }
 
@@ -96,11 +106,11 @@ extern "C" ibmc_status ibmc_check_property_noalloc(ibmc_ctx *ctx, const ibmc_mlp
         return fail(IBMC_E_INVALID, "bad k range or capacity");
     HIP_OK(hipSetDevice(ctx->device));
     IBMC_TRY(noalloc_setup(ctx->device));
-    size_t need = 0;
-    IBMC_TRY(scratch_need(ctx, net, n_deltas, opts, &need));
-    if (need > (size_t)IBMC_NOALLOC_SCRATCH_BYTES)
+    ScratchNeed N;
+    IBMC_TRY(scratch_need(ctx, net, opts, N));
+    if (N.need > (size_t)IBMC_NOALLOC_SCRATCH_BYTES)
         return fail(IBMC_E_INVALID, "this call needs up to %zu bytes of device scratch; the fixed scratch holds %zu "
-                    "(lower cex_capacity / near_tie_capacity)", need, (size_t)IBMC_NOALLOC_SCRATCH_BYTES);
+                    "(lower cex_capacity / near_tie_capacity)", N.need, (size_t)IBMC_NOALLOC_SCRATCH_BYTES);
     ibmc_property p{};
     p.net = net;
     p.image = image;
@@ -110,8 +120,8 @@ extern "C" ibmc_status ibmc_check_property_noalloc(ibmc_ctx *ctx, const ibmc_mlp
     p.k_max = opts->k_max;
     p.k_step = opts->k_step;
     // the context's own buffers step aside; empty ones carve the arena
-    DevBuf *mine[] = {&ctx->images, &ctx->props, &ctx->jobs, &ctx->u0, &ctx->prop_ids, &ctx->counters, &ctx->recs, &ctx->ties, &ctx->order, &ctx->u0f,
-                      &ctx->sortbuf, &ctx->recout};
+    DevBuf *mine[] = {&ctx->images, &ctx->props, &ctx->jobs, &ctx->u0, &ctx->prop_ids, &ctx->counters,
+                      &ctx->recs, &ctx->ties, &ctx->order, &ctx->u0f, &ctx->sortbuf, &ctx->recout};
     constexpr int NB = sizeof(mine) / sizeof(mine[0]);
     DevBuf saved[NB];
     for (int i = 0; i < NB; ++i) saved[i].swap(*mine[i]);
@@ -123,7 +133,11 @@ extern "C" ibmc_status ibmc_check_property_noalloc(ibmc_ctx *ctx, const ibmc_mlp
     arena.cap = IBMC_NOALLOC_SCRATCH_BYTES;
     ScratchArena *prev = thread_arena();
     thread_arena() = &arena;
-    const ibmc_status st = check_batch_impl(ctx, &p, 1, opts, out, cex_buf, near_tie_buf, false);
+    ibmc_status st = ctx->jobs.reserve(N.plan);
+    if (!st) st = ctx->recs.reserve(N.recs);
+    if (!st) st = ctx->sortbuf.reserve(N.sort);
+    if (!st && N.out) st = ctx->recout.reserve(N.out);
+    if (!st) st = check_batch_impl(ctx, &p, 1, opts, out, cex_buf, near_tie_buf, false);
     thread_arena() = prev;
     for (int i = 0; i < NB; ++i) {
         mine[i]->release();  // a view into the arena: nothing to free
