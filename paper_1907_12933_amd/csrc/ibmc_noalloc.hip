@@ -143,5 +143,7 @@ extern "C" ibmc_status ibmc_check_property_noalloc(ibmc_ctx *ctx, const ibmc_mlp
         mine[i]->release();  // a view into the arena: nothing to free
         mine[i]->swap(saved[i]);
     }
+    // a sigmoid table that the context did not have yet lay in the scratch too
+    if (ctx->lut.borrowed) ctx->lut.release();
     return st;
 }
