@@ -344,6 +344,24 @@ struct FoldBucket {
 constexpr double kFoldMinPoints = 30000, kFoldPoint3 = 0.35;
 constexpr size_t kFoldMaxBytes = (size_t)1 << 30;
 
+// And from this many points per property of a network on, in the mean: the scan
+// and the gather cost each property 0.1 to 2.3 us, and only points pay for them.
+// The lane kernel is as fast as the folded one on small networks, a property of
+// which pays late; the scan of three layers multiplies the second layer's rows
+// with every pixel's columns, which small layers hardly notice.  Whole calls of
+// 1,000 properties, unfolded / folded: 35-16-5 (lane) 2,450 points each 1.13 /
+// 1.37 ms, 9,660 1.38 / 1.57, 21,630 1.92 / 1.85; 35-32-10 210 points 1.02 / 0.91;
+// 20-200-10 80 points (2,000 properties) 5.6 / 5.9; 35-32-16-5 210 points 1.06 /
+// 1.14, 630 2.23 / 1.53; 196-128-64-10 392 points 1.49 / 1.65, 1,176 1.98 / 1.78;
+// 48-200-150-10 4,608 points 3.56 / 3.83, 18,240 4.98 / 4.62; 784-256-256-10 4,704
+// points 3.56 / 4.31, 25,872 4.86 / 4.74; 784-512-512-10 1,568 points 5.8 / 8.1,
+// 4,704 7.6 / 8.7, 25,872 19.7 / 10.1.
+static double fold_property_points(ibmc_ctx *ctx, const ibmc_mlp *net) {
+    if (net->L == 2) return use_lane(ctx, net, true) ? 320000.0 / net->lane.LH1 : 200.0;
+    const double n = net->dims[0];
+    return net->qd.H[1] * net->qd.H[2] <= 8192 ? std::max(400.0, 4.0 * n) : std::max(5000.0, 25.0 * n);
+}
+
 // The reduced network beats the instance the property would run on: fewer
 // matrix-core tiles per point in the hidden layers.
 static bool fold_pays(const QNetDev &q, int kw, int npair) {
@@ -384,7 +402,8 @@ static bool fold_scale(const ibmc_mlp *net, int maxe, int &f, int &halvings, int
 // clean pass done.  Nothing is folded for a
 // resumable call (its chunk numbers are part of the interface), the literal,
 // the L2 ball, a forced variant, the int32 testing aid, or when buffers come
-// from the fixed scratch array.
+// from the fixed scratch array, and no network's whose properties are too
+// small on average.
 static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, const ibmc_check_opts *o,
                                    BatchState &B, const std::vector<std::vector<int>> &level_sel, int64_t max_h1,
                                    bool resumable, std::vector<NetPlan> &plans, std::vector<FoldBucket> &buckets) {
@@ -406,24 +425,26 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
         if (!forced && !net->forced_variant.empty()) continue;
         const size_t c0 = cands.size();
         bool any_ball = false;
+        double points = 0.0;
         for (int pid : pl.ids) {
             any_ball |= B.hprops[pid].ball != 0;
             Cand c{pid, (int)nets.size(), 0, 0, 0};
             for (int li : level_sel[pid]) {
                 const int k = B.level_k[pid][li];
                 c.k = std::max(c.k, k);
-                ++n_levels;
                 if (k > 0) c.points += binom_small(net->dims[0], k) * ipow64(props[pid].n_deltas, k);
             }
             for (int j = 0; j < props[pid].n_deltas && !B.hprops[pid].ball; ++j)
                 c.maxe = std::max(c.maxe, std::min(255, std::abs((int)props[pid].deltas[j])));
+            points += (double)c.points;
             cands.push_back(c);
         }
-        if (any_ball) {
+        if (any_ball || (!forced && points < fold_property_points(ctx, net) * (double)pl.ids.size())) {
             cands.resize(c0);
             continue;
         }
-        for (size_t i = c0; i < cands.size(); ++i) est += forced ? kFoldMinPoints : cands[i].points * (net->L == 3 ? kFoldPoint3 : 1.0);
+        est += forced ? kFoldMinPoints : points * (net->L == 3 ? kFoldPoint3 : 1.0);
+        for (int pid : pl.ids) n_levels += level_sel[pid].size();
         ws_ints += pl.ids.size() * (size_t)fold_ws(net->qd.H[1], net->L == 3 ? net->qd.H[2] : 0).total;
         nets.push_back(net->qd);
         net_plan.push_back(&pl);
