@@ -113,6 +113,7 @@ struct ibmc_ctx {
     ibmc::DevBuf u0f, sortbuf;
     ibmc::PinPool pin;
     std::map<std::pair<const void *, size_t>, int> occupancy;   // resident workgroups by kernel and LDS bytes
+    ibmc::DevBuf train_rows;           // activations and deltas of a training pass (bounded)
     ibmc::DevBuf lut;                  // the table sigmoid's knots (built on first use)
     ibmc::DevBuf fold_in, fold_ws, fold_runs, fold_data;   // folded properties: see run_levels
     ibmc::DevBuf recout;  // sorted records in the public layout, on their way to a host buffer

@@ -65,10 +65,16 @@ void shuffle_epoch(uint64_t seed, int epoch, std::vector<int64_t> &ord) {
     }
 }
 
-// Buffers of passes of up to `count` samples, carved from one allocation.
-ibmc_status reserve_pass(const TrainNetDev &N, int64_t count, DevBuf &buf, TrainPassParams &P) {
+// Buffers of passes of up to `count` samples, carved from one allocation: the
+// context's up to kRowsKept bytes (allocating and freeing 2 MiB and more costs a
+// call 24 us and fresh pages), else the call's own.
+constexpr size_t kRowsKept = (size_t)16 << 20;
+
+ibmc_status reserve_pass(ibmc_ctx *ctx, const TrainNetDev &N, int64_t count, DevBuf &own, TrainPassParams &P) {
     const int64_t rows = (std::min(count, pass_cap(N, P.group)) + kTrainTile - 1) / kTrainTile * kTrainTile;
-    IBMC_TRY(buf.reserve((size_t)(2 * rows * N.units + rows) * sizeof(float)));
+    const size_t bytes = (size_t)(2 * rows * N.units + rows) * sizeof(float);
+    DevBuf &buf = bytes <= kRowsKept ? ctx->train_rows : own;
+    IBMC_TRY(buf.reserve(bytes));
     P.net = N;
     P.acts = buf.as<float>();
     P.dels = P.acts + rows * N.units;
@@ -95,7 +101,7 @@ extern "C" ibmc_status ibmc_mlp_loss_grad(ibmc_ctx *ctx, const ibmc_mlp *net, co
     IBMC_TRY(dgrad.reserve((size_t)N.n_params * 4));
     IBMC_TRY(dloss.reserve(8));
     P.group = train_group(N, kTrainMaxGroup);
-    IBMC_TRY(reserve_pass(N, n, rows, P));
+    IBMC_TRY(reserve_pass(ctx, N, n, rows, P));
     HIP_OK(launch_fill_u64(dloss.as<unsigned long long>(), 1, 0ull, s));
     P.theta = dth.as<float>();
     P.images = dimg.as<uint8_t>();
@@ -150,7 +156,7 @@ extern "C" ibmc_status ibmc_fit_mlp(ibmc_ctx *ctx, const ibmc_mlp *net, const ui
     IBMC_TRY(dord.reserve((size_t)n * 8));
     IBMC_TRY(dloss.reserve((size_t)o->epochs * 8));
     P.group = train_group(N, (int)std::min<int64_t>(kTrainMaxGroup, (B + 31) / 32));
-    IBMC_TRY(reserve_pass(N, B, rows, P));
+    IBMC_TRY(reserve_pass(ctx, N, B, rows, P));
     // a batch beyond one pass gathers its gradient before its step
     const bool whole = B <= pass_cap(N, P.group);
     if (!whole) IBMC_TRY(dgrad.reserve((size_t)N.n_params * 4));

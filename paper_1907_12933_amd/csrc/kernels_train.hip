@@ -16,14 +16,17 @@
 // sum_s delta_s a_s^T (the bias as one more input that is 1), up to 256
 // samples' rows staged in LDS in one go; a lane sums one entry, group by group
 // of samples (train_group), and takes its Adam step in place, so no gradient
-// goes through memory.
+// goes through memory.  A workgroup of its own sums the loss beside them.
 //
 // Fixed summation order, no atomics: a training run is the same on every call.
 // Measured, 35-256-128-10 at batch 256, per step: pass 25 us, weights 8 us (a
 // tile of eight samples per workgroup on the vector ALU with partial
 // gradients, their sum and the Adam step as launches of their own: 88 + 10 +
 // 5 us); an epoch of 20,000 samples 8.5 -> 3.1 ms, with the same bits.  Bound
-// by latency: the products' operations take about 1 us.  (Inputs and samples
+// by latency: the products' operations take about 1 us.  Small networks are at
+// the kernels' own latency (35-16-5, batch 1: 7 + 2.4 us a step, where the former
+// launches took 6.3 + 1.2 + 1.5; 5,000 samples in one pass: a serial sum over 20
+// stages, 91 us).  (Inputs and samples
 // split over waves and added at the end took 19 + 5 us, but rounded otherwise:
 // an epoch's loss moved by 2e-9.)
 #include "kernels_train.h"
@@ -212,6 +215,23 @@ __global__ void __launch_bounds__(256) train_weights_kernel(TrainPassParams P, T
     const TrainNetDev &N = P.net;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int U = N.units, T = P.group;
+    if (blockIdx.x == gridDim.x - 1) {
+        // the pass's loss in a fixed order: a lane per 64th group, then the lanes
+        if (wave) return;
+        double acc = 0.0;
+        for (int64_t g = lane; g * T < P.count; g += 64) {
+            float v[kTrainMaxGroup], part = 0.f;
+#pragma unroll
+            for (int z = 0; z < kTrainMaxGroup; ++z) v[z] = P.loss[min(g * T + min(z, T - 1), P.count - 1)];
+#pragma unroll
+            for (int z = 0; z < kTrainMaxGroup; ++z)
+                if (z < T && g * T + z < P.count) part += v[z];
+            acc += (double)part;
+        }
+        for (int s = 32; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
+        if (lane == 0) *A.loss_acc += acc;
+        return;
+    }
     int blk = blockIdx.x, l = 1, ti = 1;
     for (; l <= N.L; ++l) {
         ti = (N.dims[l - 1] + 16) / 16;                       // the inputs and one for the bias
@@ -230,6 +250,12 @@ __global__ void __launch_bounds__(256) train_weights_kernel(TrainPassParams P, T
     const bool mine = jr < nout && ic <= nin;
     const int64_t at = N.toff[l] + (ic < nin ? (int64_t)jr * nin + ic : (int64_t)nout * nin + jr);
     float total = mine && A.grad && A.accumulate ? A.grad[at] : 0.f;
+    float th = 0.f, mo = 0.f, ve = 0.f;                       // (read ahead of the sum)
+    if (mine && !A.grad) {
+        th = A.theta[at];
+        mo = A.mom[at];
+        ve = A.vel[at];
+    }
     const float *dr = ds + (tid >> 4) * kTrainStride, *ar = as + (tid & 15) * kTrainStride;
     const int per = kTrainStage / T * T;
     for (int64_t b = 0; b < P.count; b += per) {
@@ -237,6 +263,7 @@ __global__ void __launch_bounds__(256) train_weights_kernel(TrainPassParams P, T
         float dv[16], av[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
+            if (16 * r >= m) break;
             const int64_t s = b + min(s0 + 16 * r, m - 1);
             dv[r] = d[s * U];
             av[r] = a[s * U];
@@ -244,6 +271,7 @@ __global__ void __launch_bounds__(256) train_weights_kernel(TrainPassParams P, T
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
+            if (16 * r >= m) break;
             const int s = s0 + 16 * r;
             ds[q * kTrainStride + s] = s < m ? dv[r] : 0.f;
             as[q * kTrainStride + s] = s < m ? (one ? 1.f : av[r]) : 0.f;
@@ -279,23 +307,13 @@ __global__ void __launch_bounds__(256) train_weights_kernel(TrainPassParams P, T
         if (A.grad) {
             A.grad[at] = total;
         } else {
-            const float m = A.b1 * A.mom[at] + (1.f - A.b1) * total;
-            const float v = A.b2 * A.vel[at] + (1.f - A.b2) * total * total;
+            // (rounded as in prop_adam_kernel, wherever the loads stand)
+            const float m = fmaf(1.f - A.b1, total, A.b1 * mo);
+            const float v = fmaf(total, (1.f - A.b2) * total, A.b2 * ve);
             A.mom[at] = m;
             A.vel[at] = v;
-            A.theta[at] -= A.lr * (m / A.c1) / (sqrtf(v / A.c2) + A.eps);
+            A.theta[at] = th - A.lr * (m / A.c1) / (sqrtf(v / A.c2) + A.eps);
         }
-    }
-    if (blockIdx.x == 0 && wave == 0) {
-        // the pass's loss in a fixed order: a lane per 64th group, then the lanes
-        double acc = 0.0;
-        for (int64_t g = lane; g * T < P.count; g += 64) {
-            float part = 0.f;
-            for (int64_t s = g * T; s < min((g + 1) * T, P.count); ++s) part += P.loss[s];
-            acc += (double)part;
-        }
-        for (int s = 32; s > 0; s >>= 1) acc += __shfl_xor(acc, s);
-        if (lane == 0) *A.loss_acc += acc;
     }
 }
 
@@ -312,7 +330,7 @@ hipError_t launch_train_weights(const TrainPassParams &P, const TrainUpdate &U, 
     if (P.count <= 0) return hipSuccess;
     unsigned blocks = 0;
     for (int l = 1; l <= P.net.L; ++l) blocks += ((P.net.dims[l] + 15) / 16) * ((P.net.dims[l - 1] + 16) / 16);
-    hipLaunchKernelGGL(train_weights_kernel, dim3(blocks), dim3(256), 0, s, P, U);
+    hipLaunchKernelGGL(train_weights_kernel, dim3(blocks + 1), dim3(256), 0, s, P, U);   // (and one for the loss)
     return hipGetLastError();
 }
 
