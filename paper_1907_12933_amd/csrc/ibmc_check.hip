@@ -456,7 +456,14 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
     auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
     std::vector<FoldProp> fps(nc);
     std::vector<int32_t> map, rmap;
-    IBMC_TRY(ctx->fold_ws.reserve(al(nc * 16) + ws_ints * 4));
+    // (a call that found room before still does: without room for folding it runs unfolded)
+    auto room = [](DevBuf &b, size_t n) {
+        if (b.reserve(n) == IBMC_OK) return true;
+        (void)hipGetLastError();
+        clear_error();
+        return false;
+    };
+    if (!room(ctx->fold_ws, al(nc * 16) + ws_ints * 4)) return IBMC_OK;
     int32_t *counts = ctx->fold_ws.as<int32_t>();
     int32_t *ws = reinterpret_cast<int32_t *>(ctx->fold_ws.as<char>() + al(nc * 16));
     for (size_t i = 0; i < nc; ++i) {
@@ -486,6 +493,7 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
     memcpy(in, nets.data(), nets.size() * sizeof(QNetDev));
     memcpy((char *)in + o_fp, fps.data(), nc * sizeof(FoldProp));
     memcpy((char *)in + o_map, map.data(), map.size() * 4);
+    if (!room(ctx->fold_in, o_map + map.size() * 4)) return IBMC_OK;
     IBMC_TRY(ctx->fold_in.upload(in, o_map + map.size() * 4, s));
     const QNetDev *dnets = ctx->fold_in.as<QNetDev>();
     PropDev *dprops = ctx->props.as<PropDev>();
@@ -556,8 +564,9 @@ static ibmc_status fold_properties(ibmc_ctx *ctx, const ibmc_property *props, co
         builds.push_back(b);
     }
     if (builds.empty()) return IBMC_OK;
-    IBMC_TRY(ctx->fold_data.reserve(bytes));
-    IBMC_TRY(ctx->fold_runs.reserve(al(B.hprops.size() * sizeof(FoldRun)) + builds.size() * sizeof(FoldBuild)));
+    if (!room(ctx->fold_data, bytes) ||
+        !room(ctx->fold_runs, al(B.hprops.size() * sizeof(FoldRun)) + builds.size() * sizeof(FoldBuild)))
+        return IBMC_OK;
     char *base = ctx->fold_data.as<char>();
     for (size_t i = 0; i < builds.size(); ++i) {
         FoldRun &R = builds[i].run;
