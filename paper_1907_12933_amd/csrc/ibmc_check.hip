@@ -214,6 +214,7 @@ static ibmc_status fetch_sorted(ibmc_ctx *ctx, const DevRec *drecs, int64_t n, i
     outv.clear();
     *nout = *nall = 0;
     if (n == 0 || keep == 0) return IBMC_OK;
+    if (!direct) direct_dev = false;   // into outv, wherever the caller's own buffer is
     if (n <= kSortSmall && sort_key_bits(max_prop, max_k, max_rank) <= 64) {
         // one workgroup sorts and unpacks; the records and their number come
         // back in one copy
