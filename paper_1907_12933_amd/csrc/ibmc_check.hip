@@ -133,7 +133,6 @@ static ibmc_status send_inputs(ibmc_ctx *ctx, BatchState &B) {
     return IBMC_OK;
 }
 
-// Digits per pixel side of the L2-ball domain: min(floor(sqrt(r2)), 255).
 // Chunks per ticket of a lane kernel whose waves have n chunks each.  A ticket
 // costs a search of the job tables, about two chunks' time, and the last one
 // leaves half a ticket of waiting on average: n + 2 n / b + b / 2 is least at
@@ -143,6 +142,7 @@ static int32_t lane_batch(int64_t n) {
     return (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(64, n), (int64_t)(2.0 * std::sqrt((double)n))));
 }
 
+// Digits per pixel side of the L2-ball domain: min(floor(sqrt(r2)), 255).
 static int ball_rd(int64_t r2) {
     int64_t r = 0;
     while (r < 255 && (r + 1) * (r + 1) <= r2) ++r;
