@@ -51,3 +51,24 @@ def test_extreme_output_weights(orc, pair, layers):
         assert list(s["ties"]) == [int(v) for v in r["ties"]]
         assert np.array_equal(cex["k"], r["cex_k"]) and np.array_equal(cex["rank"], r["cex_rank"])
         assert np.array_equal(cex["new_label"], r["cex_label"])
+
+
+@pytest.mark.parametrize("layers", range(len(DIMS)))
+def test_lowest_weight_in_the_hidden_layers(orc, layers):
+    """-128 in every layer: the joint bound of layers 1 and 2, whose absolute
+    values must fit int8, is left out, and the intervals alone decide."""
+    from paper_1907_12933_amd import ibmc
+    dims, shift = DIMS[layers]
+    net, x, _ = extreme_net(orc, 50 + layers, dims, shift, (64, -64))
+    for W in net.W[:-1]:
+        W[::2, ::3] = -128
+    z = orc.q8_forward(net, x)[0][:dims[1]].astype(np.int64)
+    net.b[0] += ((128 << shift[0]) // 2 - z).astype(np.int32)   # back into the window
+    r = orc.q8_check(net, x, DELTAS, 1, 2, cap=1 << 21)
+    ctx = ibmc.Context(0)
+    m = ibmc.Mlp(ctx, net)
+    ibmc.ibmc_set_variant(ctx, m, "fold")
+    s, cex, _ = ibmc.ibmc_check_property(ctx, m, x, DELTAS, 1, 2, cex_capacity=1 << 21)
+    assert r["cex_total"] > 0
+    assert s["clean_label"] == r["clean_label"] and list(s["cex"]) == list(r["cex"]) and list(s["ties"]) == list(r["ties"])
+    assert np.array_equal(cex["rank"], r["cex_rank"]) and np.array_equal(cex["new_label"], r["cex_label"])
