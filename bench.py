@@ -25,7 +25,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 # enumeration kernel sources whose hash keys the profile record
 TUNE_TABLE = os.path.join(HERE, "paper_1907_12933_amd", "tune_gfx950.json")
 KERNEL_SOURCES = ["paper_1907_12933_amd/csrc/enum_fold_impl.h", "paper_1907_12933_amd/csrc/kernels_fold.h",
-                  "paper_1907_12933_amd/csrc/enum_fold.hip", "paper_1907_12933_amd/csrc/enum_common.h"]
+                  "paper_1907_12933_amd/csrc/fold_search.h", "paper_1907_12933_amd/csrc/enum_fold.hip",
+                  "paper_1907_12933_amd/csrc/enum_common.h"]
 
 
 def kernel_source_sha():
