@@ -1056,17 +1056,18 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         if (time_enum) HIP_OK(hipEventRecord(ctx->ek1, st));
         return IBMC_OK;
     };
-    // one more private stream (and its event) per concurrent branch
-    auto need_streams = [&](int n) -> ibmc_status {
-        while ((int)ctx->side.size() < n) {
+    // one more private stream (and its event) per concurrent branch; captured
+    // branches and ordinary ones have sets of their own
+    auto need_streams = [&](BranchSet &b, int n) -> ibmc_status {
+        while ((int)b.stream.size() < n) {
             hipStream_t ns;
             HIP_OK(hipStreamCreateWithFlags(&ns, hipStreamNonBlocking));
-            ctx->side.push_back(ns);
+            b.stream.push_back(ns);
             hipEvent_t ev;
             HIP_OK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-            ctx->side_ev.push_back(ev);
+            b.done.push_back(ev);
         }
-        if (!ctx->fork_ev) HIP_OK(hipEventCreateWithFlags(&ctx->fork_ev, hipEventDisableTiming));
+        if (!b.fork) HIP_OK(hipEventCreateWithFlags(&b.fork, hipEventDisableTiming));
         return IBMC_OK;
     };
 
@@ -1085,18 +1086,18 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         }
         const int branches = (int)buckets.size() + NN;
         if (branches > 1) {
-            IBMC_TRY(need_streams(branches));
-            HIP_OK(hipEventRecord(ctx->fork_ev, s));
+            IBMC_TRY(need_streams(ctx->fold_side, branches - 1));
+            HIP_OK(hipEventRecord(ctx->fold_side.fork, s));
         }
         ibmc_status bst = IBMC_OK;
         for (int i = 0; i < branches; ++i) {
-            hipStream_t st = i == 0 ? s : ctx->side[i];
-            if (i > 0) HIP_OK(hipStreamWaitEvent(st, ctx->fork_ev, 0));
+            hipStream_t st = i == 0 ? s : ctx->fold_side.stream[i - 1];
+            if (i > 0) HIP_OK(hipStreamWaitEvent(st, ctx->fold_side.fork, 0));
             if (bst == IBMC_OK)
                 bst = i < (int)buckets.size() ? launch_bucket(buckets[i], st) : launch_net(plans[i - buckets.size()], st);
-            if (i > 0) HIP_OK(hipEventRecord(ctx->side_ev[i], st));
+            if (i > 0) HIP_OK(hipEventRecord(ctx->fold_side.done[i - 1], st));
         }
-        for (int i = 1; i < branches; ++i) HIP_OK(hipStreamWaitEvent(s, ctx->side_ev[i], 0));
+        for (int i = 1; i < branches; ++i) HIP_OK(hipStreamWaitEvent(s, ctx->fold_side.done[i - 1], 0));
         IBMC_TRY(bst);
         timed = true;
     } else if (NN <= 1) {
@@ -1110,8 +1111,8 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
     } else {
         // one graph: a branch per network on its own stream, joined back into
         // s (the counters came cleared with the plan)
-        IBMC_TRY(need_streams(NN));
-        hipStream_t cs = ctx->side[0];  // capture origin: a private stream, never the caller's
+        IBMC_TRY(need_streams(ctx->side, NN));
+        hipStream_t cs = ctx->side.stream[0];  // capture origin: a private stream, never the caller's
         HIP_OK(hipStreamWaitEvent(cs, ctx->ek0, 0));
         // Every value the captured launches read: the plans, the buffers
         // (addresses only: their contents are uploaded before each launch)
@@ -1149,8 +1150,8 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         if (ctx->graph_exec && sig == ctx->graph_sig) {
             const hipError_t le = hipGraphLaunch(ctx->graph_exec, cs);
             if (le == hipSuccess) {
-                HIP_OK(hipEventRecord(ctx->side_ev[0], cs));
-                HIP_OK(hipStreamWaitEvent(s, ctx->side_ev[0], 0));
+                HIP_OK(hipEventRecord(ctx->side.done[0], cs));
+                HIP_OK(hipStreamWaitEvent(s, ctx->side.done[0], 0));
             }
             HIP_OK(hipStreamSynchronize(cs));
             HIP_OK(le);
@@ -1161,6 +1162,10 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         HIP_OK(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
         ibmc_status cst = IBMC_OK;
         hipError_t ce = hipSuccess;
+        // (a graph of scanned networks alone has no clean pass: one node before the
+        // fork all the same, for a counter that nothing reads)
+        if (std::all_of(plans.begin(), plans.end(), [](const NetPlan &pl) { return pl.scanned; }))
+            ce = launch_fill_u64(ctr, 1, 0ull, cs);
         // every network's clean pass first, on the origin stream: in a branch
         // it would queue behind the other branches' persistent grids, which
         // hold every compute unit until they finish
@@ -1169,14 +1174,14 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
             cst = launch_clean(plans[i], id_off, cs);
             id_off += plans[i].ids.size();
         }
-        if (ce == hipSuccess) ce = hipEventRecord(ctx->fork_ev, cs);
+        if (ce == hipSuccess) ce = hipEventRecord(ctx->side.fork, cs);
         for (int i = 0; i < NN && ce == hipSuccess && cst == IBMC_OK; ++i) {
-            hipStream_t bs = (i == 0) ? cs : ctx->side[i];
-            if (i > 0) ce = hipStreamWaitEvent(bs, ctx->fork_ev, 0);
+            hipStream_t bs = (i == 0) ? cs : ctx->side.stream[i];
+            if (i > 0) ce = hipStreamWaitEvent(bs, ctx->side.fork, 0);
             if (ce == hipSuccess) cst = launch_net(plans[i], bs);
             if (i > 0 && ce == hipSuccess && cst == IBMC_OK) {
-                ce = hipEventRecord(ctx->side_ev[i], bs);
-                if (ce == hipSuccess) ce = hipStreamWaitEvent(cs, ctx->side_ev[i], 0);
+                ce = hipEventRecord(ctx->side.done[i], bs);
+                if (ce == hipSuccess) ce = hipStreamWaitEvent(cs, ctx->side.done[i], 0);
             }
         }
         hipGraph_t graph = nullptr;
@@ -1193,8 +1198,8 @@ static ibmc_status run_levels(ibmc_ctx *ctx, const ibmc_property *props, int32_t
         ctx->graph_sig.swap(sig);
         const hipError_t le = hipGraphLaunch(exec, cs);
         if (le == hipSuccess) {
-            HIP_OK(hipEventRecord(ctx->side_ev[0], cs));
-            HIP_OK(hipStreamWaitEvent(s, ctx->side_ev[0], 0));
+            HIP_OK(hipEventRecord(ctx->side.done[0], cs));
+            HIP_OK(hipStreamWaitEvent(s, ctx->side.done[0], 0));
         }
         HIP_OK(hipStreamSynchronize(cs));
         if (le != hipSuccess) {

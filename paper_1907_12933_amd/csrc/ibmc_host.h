@@ -97,6 +97,18 @@ struct PinPool {
     void reset();                                    // every piece is given back, and the pageable memory
 };
 
+// Streams of concurrent branches (default priority) with an event each, and the
+// event they start from.
+struct BranchSet {
+    std::vector<hipStream_t> stream;
+    std::vector<hipEvent_t> done;
+    hipEvent_t fork = nullptr;
+    BranchSet() = default;
+    BranchSet(const BranchSet &) = delete;
+    BranchSet &operator=(const BranchSet &) = delete;
+    ~BranchSet();
+};
+
 }  // namespace ibmc
 
 struct ibmc_ctx {
@@ -129,9 +141,8 @@ struct ibmc_ctx {
     ibmc::DevBuf cov_img, cov_pots, cov_bits, cov_sums, cov_out;
     // tuned kernel variant per network shape key
     std::map<std::string, std::string> tuned;
-    std::vector<hipStream_t> side;     // branch streams of captured batch graphs (default priority)
-    std::vector<hipEvent_t> side_ev;
-    hipEvent_t fork_ev = nullptr;
+    ibmc::BranchSet side;              // of captured batch graphs
+    ibmc::BranchSet fold_side;         // of folded launches beside each other
     int64_t graph_launches = 0;
     // the instantiated graph of the last multi-network batch and the
     // signature of every value its launches were captured with

@@ -138,6 +138,12 @@ void PinPool::reset() {
     for (Block &b : blocks) b.used = 0;
 }
 
+BranchSet::~BranchSet() {
+    for (hipStream_t st : stream) (void)hipStreamDestroy(st);
+    for (hipEvent_t ev : done) (void)hipEventDestroy(ev);
+    if (fork) (void)hipEventDestroy(fork);
+}
+
 ibmc_status resident_blocks(ibmc_ctx *ctx, const void *fn, size_t lds, int *occ) {
     const auto key = std::make_pair(fn, lds);
     const auto it = ctx->occupancy.find(key);
@@ -220,9 +226,6 @@ ibmc_ctx::~ibmc_ctx() {
     if (flags_host) (void)hipHostFree(flags_host);
     if (stage_host) (void)hipHostFree(stage_host);
     if (stage_ev) (void)hipEventDestroy(stage_ev);
-    for (hipStream_t st : side) (void)hipStreamDestroy(st);
-    for (hipEvent_t ev : side_ev) (void)hipEventDestroy(ev);
-    if (fork_ev) (void)hipEventDestroy(fork_ev);
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
     (void)hipGetLastError();
 }
