@@ -481,7 +481,10 @@ __device__ __forceinline__ void segment_prefix(const Cursor &c, int (&pp)[kMaxK]
 // per property it keeps the clean label in a register; a chunk then loads
 // only its own pixels, deltas and first-layer rows.
 // (The waves per SIMD keep the registers that the compiler would spend on
-// addresses in check: 128-64 took 416 and ran one wave.)
+// addresses in check: 128-64 took 416 and ran one wave.  Ten table instances spill
+// under it, those of 128 units up to 480 registers; their calls take a fifth to
+// two thirds of what they took with scalar weights and no bound, 128-64-10 4.81 ->
+// 1.16 ms, 16-16-10 without scratch before 1.02 -> 0.95.)
 template <int H1, int H2, int NCP, bool TAB>
 __global__ void __launch_bounds__(256, H1 <= 16 ? 4 : H1 <= 32 ? 3 : 2) enum_f32_lane_kernel(FEnumParams P) {
     constexpr int CH = kF32LaneChunk;
